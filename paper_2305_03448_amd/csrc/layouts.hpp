@@ -97,6 +97,31 @@ DESC_HD int gemm16_frag_k(int quarter) { return quarter * (kBK / 4); }
 template <int kWTN>
 DESC_HD int gemm16_b_frag_word(int wn, int j, int c16) { return wn * kWTN + 16 * j + c16; }
 
+// Edges of the direct tile form (gemm_direct.hpp): a row past the valid
+// `rows` reads the last one; the group of kN columns that lane c of a tile
+// from column n0 owns starts at n0 + kN c, or at N - kN when it would cross
+// N (kN <= N), so every group lies inside the row.
+DESC_HD idx_t clamped_row(idx_t r, idx_t rows) { return r < rows ? r : rows - 1; }
+template <int kN>
+DESC_HD idx_t clamped_group(idx_t n0, int c, idx_t N) {
+  return n0 + kN * c + kN <= N ? n0 + kN * c : N - kN;
+}
+// Tile order over blocks dispatched round-robin over the 8 XCDs: XCD x takes
+// a contiguous run of the T tiles (the first T % 8 runs one tile longer),
+// and tiles run down groups of 8 tile rows, so the tiles in flight on one
+// XCD cover a compact patch of C and share operands in its L2.
+struct TileIndex {
+  idx_t m, n;
+};
+DESC_HD TileIndex xcd_run_tile(idx_t block, idx_t tiles_m, idx_t tiles_n) {
+  const idx_t T = tiles_m * tiles_n, x = block % 8;
+  const idx_t u = x * (T / 8) + (x < T % 8 ? x : T % 8) + block / 8;
+  constexpr idx_t kGroup = 8;
+  const idx_t g = u / (kGroup * tiles_n), r = u - g * kGroup * tiles_n;
+  const idx_t rows = tiles_m - g * kGroup < kGroup ? tiles_m - g * kGroup : kGroup;
+  return TileIndex{g * kGroup + r % rows, r / rows};
+}
+
 // Segmented forms (segmented.hip): segment s of length L_s gives
 // ceil(L_s / U) units of at most U consecutive elements; unit_start is the
 // exclusive prefix of the unit counts over the segments (S + 1 entries).

@@ -1,0 +1,62 @@
+"""The direct FP32 GEMM tile: its index maps on the host, and every form on
+the GPU at the edges of its tiles against exact integer products."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_03448_amd as desc
+import workloads
+from gpu_util import case, needs_gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2305_03448_amd", "csrc")
+
+
+def test_direct_tile_maps(tmp_path):
+    exe = str(tmp_path / "direct_tile_checks")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "direct_tile_checks.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.count("OK ") == 7, r.stdout
+
+
+FORMS = [(128, 128), (64, 128), (128, 64), (96, 96), (64, 96), (96, 64), (64, 64), (48, 64),
+         (64, 48), (48, 48), (32, 64), (64, 32), (32, 32), (16, 64), (64, 16), (16, 32), (32, 16),
+         (16, 16)]
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("bm,bn", FORMS)
+def test_direct_form_edges(bm, bn):
+    # integers: every sum is exact in FP32 in any order, so equality is asked.
+    # The padding beside A's rows and B's columns holds NaN, which must stay out.
+    op = "gemm_f32"
+    names = [desc.desc_config_name(op, c) for c in range(desc.desc_config_count(op))]
+    try:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, names.index(f"d{bm}x{bn}"))
+        for M, N, K, pad in [(bm, bn, 256, 0), (bm + 1, bn + 1, 17, 3), (bm - 1, bn - 1, 15, 1),
+                             (1, 4, 1, 0), (2 * bm + 5, 3 * bn + 2, 1041, 0), (3, 2, 33, 1),
+                             (bm, 2 * bn - 3, 0, 0), (5, bn + 2, 64, 2)]:
+            case(f"gemm f32 d{bm}x{bn} {M}x{N}x{K} pad {pad}")
+            g = workloads.rng(50)
+            A = g.integers(-4, 5, size=(M, K)).astype(np.float32)
+            B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
+
+            def padded(x):
+                t = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), device="cuda")
+                t[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+                return t[:, :x.shape[1]]
+            buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
+            desc.desc_gemm(padded(A), padded(B), buf[:M, :N])
+            want = (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32)
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[:M, :N], want)
+            assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+    finally:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, -1)
