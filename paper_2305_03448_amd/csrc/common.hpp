@@ -45,6 +45,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, kRawDword3);
 }
 
+// The thread's index through an empty asm: in the persistent loops the
+// compiler would otherwise hoist every per-lane address of an iteration out
+// of the loop and keep them live across iterations (about twice the
+// registers).
+__device__ __forceinline__ uint32_t opaque_thread() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Wait until every global memory access this wave issued has completed
 // (s_waitcnt vmcnt(0); expcnt and lgkmcnt left at their maxima).  After it a
 // device-scope atomic store is visible to every agent-scope reader.

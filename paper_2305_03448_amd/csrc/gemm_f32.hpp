@@ -230,18 +230,44 @@ __device__ __forceinline__ bool interior_tile(const GemmProblemF32& p, idx_t tm,
          vec_ok(p.A, p.lda, p.B, p.ldb);
 }
 
+// A tile the clamped form takes: any shape, alignment and edge, as long as a
+// row of B holds one group of four and the operands' spans of the tile stay
+// below 2^31 bytes.
+template <class C>
+__host__ __device__ __forceinline__ bool clamped_tile(const GemmProblemF32& p) {
+  constexpr int64_t kSpan = int64_t(1) << 29;   // elements: 2^31 bytes
+  return p.N >= 4 && p.K > 0 && (C::bm - 1) * p.lda + p.K < kSpan &&
+         (p.K - 1) * p.ldb + p.N < kSpan;
+}
+
 // kInterior (interior_tile holds): each lane's positions inside a stage are
 // the same in every stage, so its loads are fixed byte offsets in one buffer
 // range over the tile's rows of A (or columns of B) for the whole K loop,
 // and a stage moves only the scalar offset -- no address arithmetic and no
 // bounds handling per load.
-template <class C, bool kVec, bool kInterior = false>
+//
+// kClamped (clamped_tile holds; with kVec): the same loads for tiles that
+// cross the edges of C, for rows that are not whole 16-byte groups and for
+// any K.  A row past M reads row M - 1 and a group of columns that would
+// cross N starts at N - 4, so the offsets stay fixed and inside the operands
+// (the groups need 4-byte alignment only); the result of a column slot then
+// belongs to its group's shifted column, and slots past N are not stored.
+// When K is not a multiple of the stage, the first stage is the partial one:
+// it loads word by word, with the words past its share sent outside the
+// range, which reads them as zero, and every later stage is whole.  With kInterior as well:
+// the tile lies wholly inside C, whatever K and the alignment are.
+template <class C, bool kVec, bool kInterior = false, bool kClamped = false>
 __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm, idx_t tn,
                                               float* lds) {
   constexpr int BM = C::bm, BN = C::bn, BK = C::bk, T = C::threads, HK = BK / 2;
-  auto thread = thread_x<T>();
-  auto wv = wave_of_block<T>();
-  const int lane = (int)lane_of_wave().index();
+  // The clamped form runs inside loops over tiles: there the thread's index
+  // goes through an empty asm, or the compiler keeps every address derived
+  // from it in registers across the loop (200 of them instead of 150, and
+  // two blocks a CU instead of three).
+  const uint32_t tid = kClamped ? opaque_thread() : threadIdx.x;
+  const Thread<T> thread{(idx_t)tid, T};
+  const Wave<T / 64> wv{(idx_t)(tid / 64), T / 64};
+  const int lane = (int)(tid % 64);
   const int half = lane / 32, col32 = lane % 32;
   const int wm = (int)wv.index() / C::wn, wn = (int)wv.index() % C::wn;
   const idx_t m0 = tm * BM, n0 = tn * BN;
@@ -266,7 +292,27 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
   const BufferWindow<4> win_b{(uint32_t)p.ldb, (int32_t)p.K, BN};
   __amdgpu_buffer_rsrc_t rs_a, rs_b;
   uint32_t off_a[C::a_vec], off_b[C::b_vec];
-  if constexpr (kInterior) {
+  if constexpr (kClamped) {
+    // ranges over the tile's valid rows of A and over all of B
+    const idx_t rows = p.M - m0 < BM ? p.M - m0 : BM;
+    const BufferWindow<4> all_a{(uint32_t)p.lda, (int32_t)rows, (int32_t)p.K};
+    const BufferWindow<4> all_b{(uint32_t)p.ldb, (int32_t)p.K, (int32_t)p.N};
+    rs_a = buffer_rsrc(&a_g.at(m0, 0), all_a.bytes());
+    rs_b = buffer_rsrc(&b_g.at(0, 0), all_b.bytes());
+#pragma unroll
+    for (int i = 0; i < C::a_vec; ++i) {
+      const int q = (int)thread.index() + T * i;
+      off_a[i] = all_a.row((int32_t)layout::clamped_row(q / (BK / 4), rows)) +
+                 all_a.col_valid(4 * (q % (BK / 4)));
+    }
+#pragma unroll
+    for (int i = 0; i < C::b_vec; ++i) {
+      const int q = (int)thread.index() + T * i;
+      off_b[i] = all_b.row(q / (BN / 4)) +
+                 all_b.col_valid((int32_t)layout::clamped_group<4>(n0, q % (BN / 4), p.N));
+    }
+  }
+  if constexpr (kInterior && !kClamped) {
     rs_a = buffer_rsrc(&a_g.at(m0, 0), win_a.bytes());
     rs_b = buffer_rsrc(&b_g.at(0, n0), win_b.bytes());
 #pragma unroll
@@ -280,8 +326,23 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
       off_b[i] = win_b.offset(q / (BN / 4), 4 * (q % (BN / 4)));
     }
   }
+  // the clamped form's first stage lacks this many values of its BK
+  const idx_t short_by = kClamped && p.K % BK != 0 ? BK - p.K % BK : 0;
   auto load = [&](idx_t kt, Regs& R) {
     const idx_t k0 = kt * BK;
+    if constexpr (kClamped) {
+      const idx_t k0 = kt * BK - short_by;
+      const int sa = (int)win_a.col_valid((int32_t)k0), sb = (int)win_b.row((int32_t)k0);
+#pragma unroll
+      for (int i = 0; i < C::a_vec; ++i)
+        R.a[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_a, (int)off_a[i],
+                                                                                  sa, 0));
+#pragma unroll
+      for (int i = 0; i < C::b_vec; ++i)
+        R.b[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_b, (int)off_b[i],
+                                                                                  sb, 0));
+      return;
+    }
     if constexpr (kInterior) {
       // stage kt: k0 columns into A's range, k0 rows into B's
       const int sa = (int)win_a.col_valid((int32_t)k0), sb = (int)win_b.row((int32_t)k0);
@@ -322,6 +383,25 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
 #pragma unroll
         for (int j = 0; j < 4; ++j) R.b[i][j] = (r < p.K && c + j < p.N) ? b_g.at(r, c + j) : 0.f;
       }
+    }
+  };
+  // that first stage: the first `left` values of K
+  auto load_part = [&](int left, Regs& R) {
+#pragma unroll
+    for (int i = 0; i < C::a_vec; ++i) {
+      const int c = 4 * (((int)thread.index() + T * i) % (BK / 4));
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        R.a[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+            rs_a, (int)(c + j < left ? off_a[i] + 4 * j : kOutside), 0, 0));
+    }
+#pragma unroll
+    for (int i = 0; i < C::b_vec; ++i) {
+      const int r = ((int)thread.index() + T * i) / (BN / 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        R.b[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+            rs_b, (int)(r < left ? off_b[i] + 4 * j : kOutside), 0, 0));
     }
   };
   auto store = [&](const Regs& R, int buf) {
@@ -396,6 +476,7 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
   };
 
   const idx_t nk = (p.K + BK - 1) / BK;
+  static_assert(!kClamped || C::depth == 2, "the clamped form's first stage");
   if constexpr (C::depth == 1) {
     // stage kt+1's loads are issued before stage kt's matrix ops
     if (nk > 0) {
@@ -415,7 +496,8 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
     // stage kt and writes stage kt+1 (loaded one iteration earlier); pairs
     // of iterations name their register sets statically
     if (nk > 0) {
-      load(0, R0);
+      if (short_by > 0) load_part((int)(BK - short_by), R0);
+      else load(0, R0);
       store(R0, 0);
     }
     if (nk > 1) load(1, R1);
@@ -463,13 +545,28 @@ __device__ __forceinline__ void tile_rowmajor(const GemmProblemF32& p, idx_t tm,
     if constexpr (C::k16) return n0 + wn * C::wtn + j * 16 + lane % 16;
     else return n0 + wn * C::wtn + j * 32 + col32;
   };
-  if (m0 + BM <= p.M && n0 + BN <= p.N) {
+  if ((kInterior && kClamped) || (m0 + BM <= p.M && n0 + BN <= p.N)) {
 #pragma unroll
     for (int i = 0; i < C::fm; ++i)
 #pragma unroll
       for (int j = 0; j < C::fn; ++j)
 #pragma unroll
         for (int r = 0; r < C::acc_regs; ++r) c_g.at(acc_row(i, r), acc_col(j)) = acc[i][j][r];
+  } else if constexpr (kClamped) {
+#pragma unroll
+    for (int j = 0; j < C::fn; ++j) {
+      // the slot's group of four columns, from its clamped start
+      const int slot = (int)(acc_col(j) - n0);
+      const bool in = n0 + slot / 4 * 4 < p.N;
+      const idx_t col = layout::clamped_group<4>(n0, slot / 4, p.N) + slot % 4;
+#pragma unroll
+      for (int i = 0; i < C::fm; ++i)
+#pragma unroll
+        for (int r = 0; r < C::acc_regs; ++r) {
+          const idx_t row = acc_row(i, r);
+          if (row < p.M && in) c_g.at(row, col) = acc[i][j][r];
+        }
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < C::fm; ++i)

@@ -34,13 +34,21 @@ namespace {
 constexpr int kBlock = 256;
 using BigTile = GemmCfgF32<128, 128, 16>;
 using SmallTile = GemmCfgF32<64, 64, 16>;
-using SmallTileRm = gemm_f32::GemmCfgF32W<64, 64, 16, 2, 2, 2, true>;   // row-major A, two stages ahead, 16x16x4
 
 struct GroupedWs {
   int64_t* total;        // tiles over all problems
   int64_t* tile_start;   // [G + 1], in planned order
   int32_t* order;        // [G] problem index in planned order
-  int32_t* big;          // [G] 1 if the problem uses the large tile (indexed by problem)
+  int32_t* big;          // [G] 1 if the problem may use the large tile (indexed by problem)
+};
+
+// The mixed tiles' plan, in the same places: prefixes of both tile counts in
+// planned order, which tile_start and big hold in the other configurations.
+struct MixWs {
+  int64_t* total;        // [0] small tiles, [1] large tiles
+  int64_t* small_start;  // [G + 1]
+  int32_t* big_start;    // [G]
+  int32_t* order;        // [G]
 };
 
 // A problem takes the large tile when both M and N are at least big_min.
@@ -82,8 +90,9 @@ __device__ __forceinline__ int64_t block_excl(int64_t v, int64_t* excl, int64_t*
 // every lane reads one boundary and a ballot counts those <= t (a prefix of
 // the lanes), so G = 512 takes two rounds of parallel loads instead of nine
 // dependent ones.
-__device__ __forceinline__ idx_t wave_owner(const int64_t* start, int64_t G, int64_t t) {
-  auto st = array(start, G + 1);
+template <class T>
+__device__ __forceinline__ idx_t wave_owner(const T* start, int64_t G, int64_t t) {
+  auto st = array(start, G);
   const idx_t lane = lane_of_wave().index();
   idx_t lo = 0, hi = G;
   while (hi - lo > 1) {
@@ -169,17 +178,14 @@ __global__ __launch_bounds__(kBlock) void grouped_plan_kernel(const desc_gemm_pr
 
 // kBig: whether any problem may use the large tile (the LDS is sized for the
 // largest tile the launch can meet, which bounds how many blocks fit a CU).
-// kRm: 64 x 64 tiles of the row-major-A tile form.
-template <bool kBig, bool kRm = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kRm ? 3 : 1)))
-void grouped_gemm_kernel(const desc_gemm_problem* probs,
+template <bool kBig>
+__global__ __launch_bounds__(kBlock) void grouped_gemm_kernel(const desc_gemm_problem* probs,
                                                               int64_t G, const int64_t* total,
                                                               const int64_t* tile_start,
                                                               const int32_t* order,
                                                               const int32_t* big) {
   __shared__ __attribute__((aligned(16))) float
-      lds[kRm ? SmallTileRm::lds_floats
-              : (kBig ? gemm_f32::lds_floats<BigTile>() : gemm_f32::lds_floats<SmallTile>())];
+      lds[kBig ? gemm_f32::lds_floats<BigTile>() : gemm_f32::lds_floats<SmallTile>()];
   __shared__ int64_t s_slot;
   auto block = block_x();
   auto thread = thread_x<kBlock>();
@@ -204,15 +210,7 @@ void grouped_gemm_kernel(const desc_gemm_problem* probs,
     const GemmProblemF32 q{p.A, p.lda, p.B, p.ldb, p.C, p.ldc, p.M, p.N, p.K};
     const idx_t local = t - ts[slot];
     const bool vec = gemm_f32::vec_ok(p.A, p.lda, p.B, p.ldb);
-    if constexpr (kRm) {
-      const idx_t tn = (p.N + 63) / 64, tm_ = local / tn, tn_ = local % tn;
-      if (vec && gemm_f32::interior_tile<SmallTileRm>(q, tm_, tn_))
-        gemm_f32::tile_rowmajor<SmallTileRm, true, true>(q, tm_, tn_, lds);
-      else if (vec && p.K % 4 == 0 && p.N % 4 == 0 && p.K > 0)
-        gemm_f32::tile_rowmajor<SmallTileRm, true>(q, tm_, tn_, lds);
-      else
-        gemm_f32::tile_rowmajor<SmallTileRm, false>(q, tm_, tn_, lds);
-    } else if (kBig && b) {
+    if (kBig && b) {
       const idx_t tn = (p.N + 127) / 128;
       if (vec) gemm_f32::tile<BigTile, true>(q, local / tn, local % tn, lds);
       else gemm_f32::tile<BigTile, false>(q, local / tn, local % tn, lds);
@@ -222,6 +220,199 @@ void grouped_gemm_kernel(const desc_gemm_problem* probs,
       else gemm_f32::tile<SmallTile, false>(q, local / tn, local % tn, lds);
     }
     sync(thread);   // s_slot and lds are reused by the next tile
+  }
+}
+
+// --------------------------------------------------------------------------
+// Mixed tiles (the tuned configuration).  A problem is cut into as many whole
+// 128 x 128 tiles as it holds and 64 x 64 tiles over what is left on its
+// right and bottom, all in the clamped LDS-staged form: 16-byte loads
+// whatever the alignment, and no matrix work on padding when M and N are
+// multiples of 64.  All large tiles come first and then all small ones, both
+// by K descending.
+//
+// The walk is fixed (layout::tile_walk in short runs): handing tiles out by
+// atomic counters, one per XCD, was no faster on 512 mixed problems and lost
+// 30 % on small ones, since a returning atomic at the start of a tile holds
+// up that tile's first loads.  The prefixes of tile counts are kept in LDS
+// (up to kMixLdsProblems problems), where a step of the search for a tile's
+// problem costs tens of cycles instead of a trip to L2.
+using MixBig = gemm_f32::GemmCfgF32W<128, 128, 16, 2, 2, 2, true>;
+using MixSmall = gemm_f32::GemmCfgF32W<64, 64, 16, 2, 2, 2, true>;
+constexpr int kMixBuckets = 33;                  // K > 2048, then 64 at a time
+constexpr int kMixLdsProblems = 1024;
+constexpr idx_t kMixRun = 16;
+// Whole 128 x 128 tiles over all problems from which they are used: one for
+// three CUs in four.
+constexpr int64_t kMixMinBig = 192;
+
+struct MixPlan {
+  idx_t big_m, big_n, n64;      // large tiles down and across; 64-wide tiles over N
+  idx_t bigs, right, smalls;
+};
+// The tiles of a problem: `bigs` whole large tiles row by row; as small ones
+// the 64-wide strip of the columns right of them over all rows (`right`),
+// then the strip of the rows below them over their columns.
+__device__ __forceinline__ MixPlan mix_plan(const GemmProblemF32& p, bool use_big) {
+  MixPlan m{0, 0, 0, 0, 0, 0};
+  if (p.M <= 0 || p.N <= 0 || p.K < 0) return m;
+  const idx_t m64 = (p.M + 63) / 64;
+  m.n64 = (p.N + 63) / 64;
+  if (use_big && p.M >= 128 && p.N >= 128 && gemm_f32::clamped_tile<MixBig>(p)) {
+    m.big_m = p.M / 128;
+    m.big_n = p.N / 128;
+  }
+  m.bigs = m.big_m * m.big_n;
+  m.right = m64 * (m.n64 - 2 * m.big_n);
+  m.smalls = m.right + (m64 - 2 * m.big_m) * 2 * m.big_n;
+  return m;
+}
+
+__device__ __forceinline__ GemmProblemF32 as_f32(const desc_gemm_problem& p) {
+  return GemmProblemF32{p.A, p.lda, p.B, p.ldb, p.C, p.ldc, p.M, p.N, p.K};
+}
+__device__ __forceinline__ int mix_key(const desc_gemm_problem& p) {
+  const int64_t kb = p.K <= 0 ? 0 : (p.K - 1) / 64;
+  return kMixBuckets - 1 - (int)(kb < kMixBuckets - 1 ? kb : kMixBuckets - 1);
+}
+
+__global__ __launch_bounds__(kBlock) void grouped_plan_mixed_kernel(const desc_gemm_problem* probs,
+                                                                    int64_t G, MixWs w) {
+  __shared__ int64_t lds[kBlock / kWave];
+  __shared__ int32_t s_pos[kMixBuckets];
+  auto thread = thread_x<kBlock>();
+  auto pr = array(probs, G);
+  auto ord = array(w.order, G);
+  if (thread.index() < kMixBuckets) s_pos[thread.index()] = 0;
+  sync(thread);
+  // large tiles over all problems, and the problems per bucket of K
+  int64_t bigs = 0, ex = 0;
+  for (idx_t g = thread.index(); g < G; g += kBlock) {
+    const desc_gemm_problem p = pr[g];
+    bigs += mix_plan(as_f32(p), true).bigs;
+    atomicAdd(&s_pos[mix_key(p)], 1);
+  }
+  const bool use_big = block_excl(bigs, &ex, lds) >= kMixMinBig;
+  if (thread.index() == 0) {
+    int32_t at = 0;
+    for (int k = 0; k < kMixBuckets; ++k) {
+      const int32_t c = s_pos[k];
+      s_pos[k] = at;
+      at += c;
+    }
+  }
+  sync(thread);
+  // longest K first (the order within a bucket varies from run to run, which
+  // changes only which block computes a tile)
+  for (idx_t g = thread.index(); g < G; g += kBlock)
+    ord[atomicAdd(&s_pos[mix_key(pr[g])], 1)] = (int32_t)g;
+  sync(thread);
+  int64_t c_big = 0, c_small = 0;
+  for (idx_t base = 0; base < G; base += kBlock) {
+    const idx_t i = base + thread.index();
+    MixPlan m{0, 0, 0, 0, 0, 0};
+    if (i < G) m = mix_plan(as_f32(pr[ord[i]]), use_big);
+    int64_t e_small;
+    const int64_t t_big = block_excl(m.bigs, &ex, lds);
+    const int64_t t_small = block_excl(m.smalls, &e_small, lds);
+    if (i < G) {
+      array(w.big_start, G)[i] = (int32_t)(c_big + ex);
+      array(w.small_start, G + 1)[i] = c_small + e_small;
+    }
+    c_big += t_big;
+    c_small += t_small;
+  }
+  if (thread.index() == 0) {
+    array(w.small_start, G + 1)[G] = c_small;
+    w.total[0] = c_small;
+    w.total[1] = c_big;
+  }
+}
+
+// The form for strides or rows the clamped tile does not take; out of line,
+// since its guarded loads would cost the kernel its registers.
+__device__ __attribute__((noinline)) void guarded_tile(const GemmProblemF32 q, idx_t tm, idx_t tn,
+                                                       float* lds) {
+  gemm_f32::tile_rowmajor<MixSmall, false>(q, tm, tn, lds);
+}
+
+// The problem at a planned slot, in scalar registers: the loads are vector
+// ones (the compiler cannot tell that the memory is constant), and the tile
+// would keep every address it derives from them in vector registers (200 of
+// them instead of 150 for the 128 x 128 tile).
+__device__ __forceinline__ GemmProblemF32 planned_problem(const desc_gemm_problem* probs,
+                                                          const int32_t* order, int64_t G,
+                                                          idx_t slot) {
+  const desc_gemm_problem p =
+      array(probs, G)[__builtin_amdgcn_readfirstlane(array(order, G)[slot])];
+  return GemmProblemF32{(const float*)wave::uniform_i64((int64_t)p.A), wave::uniform_i64(p.lda),
+                        (const float*)wave::uniform_i64((int64_t)p.B), wave::uniform_i64(p.ldb),
+                        (float*)wave::uniform_i64((int64_t)p.C), wave::uniform_i64(p.ldc),
+                        wave::uniform_i64(p.M), wave::uniform_i64(p.N), wave::uniform_i64(p.K)};
+}
+
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+void grouped_mixed_kernel(const desc_gemm_problem* probs, int64_t G, MixWs w) {
+  __shared__ __attribute__((aligned(16))) float lds[MixBig::lds_floats];
+  __shared__ int64_t s_start[kMixLdsProblems + 1];
+  __shared__ int64_t s_slot;
+  auto block = block_x();
+  auto thread = thread_x<kBlock>();
+  const int64_t TS = w.total[0], TB = w.total[1];
+  const bool in_lds = G <= kMixLdsProblems;
+  if (in_lds) {
+    for (idx_t i = thread.index(); i <= G; i += kBlock)
+      s_start[i] = i < G ? array(w.big_start, G)[i] : TB;
+    sync(thread);
+  }
+  const layout::TileWalk walk = layout::tile_walk(block.index(), block.count());
+  idx_t l = walk.first;
+  for (;; l += walk.per) {
+    const idx_t t = walk.tile<kMixRun>(l);
+    if (t >= TB) break;
+    if (thread.index() < kWave) {    // planned slot of tile t: last i with start[i] <= t
+      const idx_t slot = in_lds ? wave_owner(s_start, G, t) : wave_owner(w.big_start, G, t);
+      if (thread.index() == 0) s_slot = slot;
+    }
+    sync(thread);
+    const idx_t slot = wave::uniform_i64(s_slot);
+    const GemmProblemF32 q = planned_problem(probs, w.order, G, slot);
+    const idx_t local = t - (idx_t)array(w.big_start, G)[slot], across = q.N / 128;
+    gemm_f32::tile_rowmajor<MixBig, true, true, true>(q, wave::uniform_i64(local / across),
+                                                      wave::uniform_i64(local % across), lds);
+    sync(thread);                    // s_slot and lds are reused by the next tile
+  }
+  if (in_lds) {
+    for (idx_t i = thread.index(); i <= G; i += kBlock) s_start[i] = array(w.small_start, G + 1)[i];
+    sync(thread);
+  }
+  for (;; l += walk.per) {
+    const idx_t t = walk.tile<kMixRun>(l) - TB;
+    if (t >= TS) break;
+    if (thread.index() < kWave) {
+      const idx_t slot = in_lds ? wave_owner(s_start, G, t) : wave_owner(w.small_start, G, t);
+      if (thread.index() == 0) s_slot = slot;
+    }
+    sync(thread);
+    const idx_t slot = wave::uniform_i64(s_slot);
+    const GemmProblemF32 q = planned_problem(probs, w.order, G, slot);
+    const MixPlan m = mix_plan(q, TB > 0);
+    const idx_t e = t - array(w.small_start, G + 1)[slot], wide = m.n64 - 2 * m.big_n;
+    idx_t tm, tn;                    // in tiles of 64
+    if (e < m.right) {
+      tm = e / wide;
+      tn = 2 * m.big_n + e % wide;
+    } else {
+      tm = 2 * m.big_m + (e - m.right) / (2 * m.big_n);
+      tn = (e - m.right) % (2 * m.big_n);
+    }
+    tm = wave::uniform_i64(tm);
+    tn = wave::uniform_i64(tn);
+    if (gemm_f32::clamped_tile<MixSmall>(q))
+      gemm_f32::tile_rowmajor<MixSmall, true, false, true>(q, tm, tn, lds);
+    else
+      guarded_tile(q, tm, tn, lds);
+    sync(thread);
   }
 }
 
@@ -238,10 +429,10 @@ GroupedWs carve(void* ws, int64_t G) {
   return r;
 }
 
-template <bool kBig, bool kRm>
+template <bool kBig>
 int persistent_grid() {
   static int cached[64] = {0};
-  return launch::resident_grid(grouped_gemm_kernel<kBig, kRm>, cached, 1, kBlock);
+  return launch::resident_grid(grouped_gemm_kernel<kBig>, cached, 1, kBlock);
 }
 
 // --------------------------------------------------------------------------
@@ -671,12 +862,12 @@ hipError_t launch_bf16x3(const desc_gemm_problem* problems, int64_t G, const Bf1
 }
 
 // FP32 tile choice: 128 x 128 tiles for problems with M, N >= 256 and 64 x 64
-// otherwise, or 64 x 64 tiles throughout (more, smaller tiles balance better
-// over the CUs when the problems are small), in the first or the row-major-A
-// tile form.
+// otherwise, or 64 x 64 tiles throughout, in the first tile form; or the
+// mixed tiles (the name is the one that saved tables know, from the row-major
+// 64 x 64 tiles that the mixed ones replaced).
 constexpr const char* kNames[] = {"tile128_or_64", "tile64", "tile64_rm_d2"};
 constexpr int kDefaults[tune::kClasses] = {1, 1, 1, 1};
-constexpr int64_t kBigMin[] = {256, INT64_MAX, INT64_MAX};
+constexpr int64_t kBigMin[] = {256, INT64_MAX};
 const bool kRegistered =
     (tune::register_op(tune::kGemmGrouped, "gemm_grouped", 3, kNames, kDefaults), true);
 
@@ -743,21 +934,23 @@ hipError_t gemm_grouped_f32(const desc_gemm_problem* problems, int64_t G, void* 
   const GroupedWs w = carve(ws, G);
   // the size class is taken from the problem count
   const int cfg = tune::get(tune::kGemmGrouped, tune::size_class(tune::kGemmGrouped, G));
+  if (cfg == 2) {
+    static int mixed_grid[64] = {0};
+    const MixWs m{w.total, w.tile_start, w.big, w.order};
+    const int grid = launch::resident_grid(grouped_mixed_kernel, mixed_grid, 1, kBlock);
+    hipLaunchKernelGGL(grouped_plan_mixed_kernel, dim3(1), dim3(kBlock), 0, s, problems, G, m);
+    hipLaunchKernelGGL(grouped_mixed_kernel, dim3((unsigned)grid), dim3(kBlock), 0, s, problems,
+                       G, m);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(grouped_plan_kernel, dim3(1), dim3(kBlock), 0, s, problems, G,
-                     kBigMin[cfg >= 0 && cfg < 3 ? cfg : 1], w.total, w.tile_start, w.order,
-                     w.big);
-  if (cfg == 2)
-    hipLaunchKernelGGL((grouped_gemm_kernel<false, true>),
-                       dim3((unsigned)persistent_grid<false, true>()), dim3(kBlock), 0, s,
-                       problems, G, w.total, w.tile_start, w.order, w.big);
-  else if (cfg == 1)
-    hipLaunchKernelGGL((grouped_gemm_kernel<false, false>),
-                       dim3((unsigned)persistent_grid<false, false>()), dim3(kBlock), 0, s,
-                       problems, G, w.total, w.tile_start, w.order, w.big);
+                     kBigMin[cfg == 0 ? 0 : 1], w.total, w.tile_start, w.order, w.big);
+  if (cfg == 1)
+    hipLaunchKernelGGL(grouped_gemm_kernel<false>, dim3((unsigned)persistent_grid<false>()),
+                       dim3(kBlock), 0, s, problems, G, w.total, w.tile_start, w.order, w.big);
   else
-    hipLaunchKernelGGL((grouped_gemm_kernel<true, false>),
-                       dim3((unsigned)persistent_grid<true, false>()), dim3(kBlock), 0, s,
-                       problems, G, w.total, w.tile_start, w.order, w.big);
+    hipLaunchKernelGGL(grouped_gemm_kernel<true>, dim3((unsigned)persistent_grid<true>()),
+                       dim3(kBlock), 0, s, problems, G, w.total, w.tile_start, w.order, w.big);
   return hipGetLastError();
 }
 

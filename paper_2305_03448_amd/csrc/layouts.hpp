@@ -173,8 +173,9 @@ DESC_HD bool lookback_in_segment(idx_t j, idx_t window, int lane) { return 64 * 
 struct TileWalk {
   idx_t first, per, xcd;
   bool by_xcd;
+  template <idx_t kRun = 64>
   DESC_HD idx_t tile(idx_t l) const {
-    return by_xcd ? (8 * (l / 64) + xcd) * 64 + l % 64 : l;
+    return by_xcd ? (8 * (l / kRun) + xcd) * kRun + l % kRun : l;
   }
 };
 DESC_HD TileWalk tile_walk(idx_t block, idx_t blocks) {

@@ -233,16 +233,6 @@ __device__ __forceinline__ int32_t lds_unit_plan(const int64_t* offsets, int64_t
   return total;
 }
 
-// The thread's wave and lane, through an empty asm: in the persistent
-// loops the compiler would otherwise hoist every per-lane address of a unit
-// out of the loop and keep them live across units (about twice the
-// registers).
-__device__ __forceinline__ uint32_t opaque_thread() {
-  uint32_t t = threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 // The unit's elements as [waves][rounds][lanes][4]; x[r][k] gets element
 // (w * rounds + r) * 256 + lane * 4 + k (0 beyond the unit's length).
 // kNt: non-temporal 16-byte loads (the reduce, which only streams its input;

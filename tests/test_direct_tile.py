@@ -1,5 +1,6 @@
-"""The direct FP32 GEMM tile: its index maps on the host, and every form on
-the GPU at the edges of its tiles against exact integer products."""
+"""The direct FP32 GEMM tile and the clamped LDS-staged one: their index maps on
+the host, every form on the GPU at the edges of its tiles, and the mixed tiles
+of the grouped GEMM, against exact integer products."""
 import os
 import subprocess
 
@@ -30,19 +31,19 @@ FORMS = [(128, 128), (64, 128), (128, 64), (96, 96), (64, 96), (96, 64), (64, 64
 
 @pytest.mark.gpu
 @needs_gpu
-@pytest.mark.parametrize("bm,bn", FORMS)
-def test_direct_form_edges(bm, bn):
+@pytest.mark.parametrize("bm,bn,name", [(m, n, f"d{m}x{n}") for m, n in FORMS])
+def test_direct_form_edges(bm, bn, name):
     # integers: every sum is exact in FP32 in any order, so equality is asked.
     # The padding beside A's rows and B's columns holds NaN, which must stay out.
     op = "gemm_f32"
     names = [desc.desc_config_name(op, c) for c in range(desc.desc_config_count(op))]
     try:
         for cls in range(4):
-            desc.desc_config_set(op, cls, names.index(f"d{bm}x{bn}"))
+            desc.desc_config_set(op, cls, names.index(name))
         for M, N, K, pad in [(bm, bn, 256, 0), (bm + 1, bn + 1, 17, 3), (bm - 1, bn - 1, 15, 1),
                              (1, 4, 1, 0), (2 * bm + 5, 3 * bn + 2, 1041, 0), (3, 2, 33, 1),
                              (bm, 2 * bn - 3, 0, 0), (5, bn + 2, 64, 2)]:
-            case(f"gemm f32 d{bm}x{bn} {M}x{N}x{K} pad {pad}")
+            case(f"gemm f32 {name} {M}x{N}x{K} pad {pad}")
             g = workloads.rng(50)
             A = g.integers(-4, 5, size=(M, K)).astype(np.float32)
             B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
@@ -60,3 +61,41 @@ def test_direct_form_edges(bm, bn):
     finally:
         for cls in range(4):
             desc.desc_config_set(op, cls, -1)
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("count", [1, 45, 1100])   # small tiles; both sizes; prefixes outside LDS
+def test_grouped_mixed_tiles(count):
+    # odd shapes and strides, NaN beside every row, K = 0, N below a group of
+    # four, whole tiles, a row stride beyond the tiles' 2^31-byte spans
+    case(f"grouped f32 mixed tiles, {count} problems")
+    g = workloads.rng(51)
+    edge = [(128, 128, 16), (129, 255, 33), (300, 3, 70), (5, 700, 0), (384, 256, 160), (1, 1, 1)]
+    top = 400 if count < 1000 else 40
+    shapes = (edge + [tuple(int(v) for v in g.integers(1, top, size=3)) for _ in range(count)])
+    # enough whole 128 x 128 tiles for the large form
+    shapes = shapes[:count] if count == 1 else shapes[:count] + [(1024, 1536, 50), (1000, 1800, 48)]
+    problems, want, bufs = [], [], []
+    for i, (M, N, K) in enumerate(shapes):
+        A = g.integers(-4, 5, size=(M, K)).astype(np.float32)
+        B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
+        pad = i % 3
+
+        def padded(x, ld=0):
+            t = torch.full((x.shape[0], max(x.shape[1] + pad, ld)), float("nan"), device="cuda")
+            t[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+            return t[:, :x.shape[1]]
+        buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
+        # rows of A 2^24 floats apart: 64 of them span 2^32 bytes
+        ld = 1 << 24 if count == 45 and (M, N, K) == (129, 255, 33) else 0
+        problems.append((padded(A, ld), padded(B), buf[:M, :N]))
+        bufs.append(buf)
+        want.append((A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32))
+    d = desc.grouped_descriptors(problems, torch.device("cuda"))
+    desc.desc_gemm_grouped(d, mode="f32")
+    torch.cuda.synchronize()
+    for (M, N, K), buf, w in zip(shapes, bufs, want):
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[:M, :N], w), (M, N, K)
+        assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
