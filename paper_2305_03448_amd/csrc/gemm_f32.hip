@@ -52,6 +52,22 @@ void gemm_f32w_kernel(
     gemm_f32::tile_rowmajor<C, kVec>(p, tm, tn, lds);
 }
 
+// The clamped form (gemm_f32.hpp): tiles inside C, and the ones at its edges.
+template <class C>
+__global__ __launch_bounds__(C::threads) __attribute__((amdgpu_waves_per_eu(C::depth)))
+void gemm_f32c_kernel(
+    const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+    float* __restrict__ Cm, int64_t ldc, int64_t M, int64_t N, int64_t K) {
+  __shared__ __attribute__((aligned(16))) float lds[C::lds_floats];
+  const GemmProblemF32 p{A, lda, B, ldb, Cm, ldc, M, N, K};
+  const auto t = layout::xcd_run_tile(block_x().index(), (M + C::bm - 1) / C::bm,
+                                      (N + C::bn - 1) / C::bn);
+  if ((t.m + 1) * C::bm <= M && (t.n + 1) * C::bn <= N)
+    gemm_f32::tile_rowmajor<C, true, true, true>(p, t.m, t.n, lds);
+  else
+    gemm_f32::tile_rowmajor<C, true, false, true>(p, t.m, t.n, lds);
+}
+
 template <class C>
 hipError_t launch_gemm_w(const float* A, int64_t lda, const float* B, int64_t ldb, float* Cm,
                          int64_t ldc, int64_t M, int64_t N, int64_t K, hipStream_t s) {
@@ -63,6 +79,17 @@ hipError_t launch_gemm_w(const float* A, int64_t lda, const float* B, int64_t ld
   else
     hipLaunchKernelGGL((gemm_f32w_kernel<C, false>), dim3((unsigned)tiles), dim3(C::threads), 0,
                        s, A, lda, B, ldb, Cm, ldc, M, N, K);
+  return hipGetLastError();
+}
+
+// The clamped form where the call's spans allow it, else the guarded one.
+template <class C>
+hipError_t launch_gemm_c(const GemmProblemF32& g, hipStream_t s) {
+  if (!gemm_f32::clamped_tile<C>(g))
+    return launch_gemm_w<C>(g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K, s);
+  const int64_t tiles = ((g.M + C::bm - 1) / C::bm) * ((g.N + C::bn - 1) / C::bn);
+  hipLaunchKernelGGL(gemm_f32c_kernel<C>, dim3((unsigned)tiles), dim3(C::threads), 0, s, g.A,
+                     g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K);
   return hipGetLastError();
 }
 
@@ -153,7 +180,8 @@ constexpr DirectForm kDirect[] = {
 constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
 
 // A call's time as rounds of 256 tiles, each K steps and the start and end
-// of its tiles (measured 2-2.5 us a round at K = 64, whatever the tile).
+// of its tiles: measured at K = 64, 2.0 us a round for 64 x 64 and smaller
+// tiles, 2.5 for 64 x 128, 3.5 for 128 x 128.
 double rounds_us(int64_t M, int64_t N, int64_t K, int bm, int bn, double ns_per_k, double ends) {
   const double tiles = (double)((M + bm - 1) / bm) * (double)((N + bn - 1) / bn);
   const double rounds = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
@@ -163,10 +191,10 @@ double rounds_us(int64_t M, int64_t N, int64_t K, int bm, int bn, double ns_per_
 // The fastest direct form by that estimate (a 16 x 16 tile takes any N).
 const DirectForm& best_direct(int64_t M, int64_t N, int64_t K, double* us) {
   const DirectForm* best = &kDirect[kDirectForms - 1];
-  *us = rounds_us(M, N, K, best->bm, best->bn, best->ns_per_k, 2.2);
+  *us = 1e300;
   for (const DirectForm& f : kDirect) {
     if (N < f.cols) continue;
-    const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, 2.2);
+    const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, 1.5 + f.bm * f.bn / 8192.0);
     if (t < *us) { best = &f; *us = t; }
   }
   return *best;
@@ -182,9 +210,12 @@ constexpr const char* kNames[] = {"m128n128k16", "m256n128k16", "m128n128k32", "
                                   "m256n128k16_rm_d2_x16", "by_shape",
                                   "d128x128", "d64x128", "d128x64", "d96x96", "d64x96", "d96x64",
                                   "d64x64", "d48x64", "d64x48", "d48x48", "d32x64", "d64x32",
-                                  "d32x32", "d16x64", "d64x16", "d16x32", "d32x16", "d16x16"};
+                                  "d32x32", "d16x64", "d64x16", "d16x32", "d32x16", "d16x16",
+                                  "m128n128k16_c"};
 constexpr int kByShape = 11, kCount = (int)(sizeof(kNames) / sizeof(kNames[0]));
-static_assert(kCount == kByShape + 1 + kDirectForms, "one name per configuration");
+constexpr int kClamped = kByShape + 1 + kDirectForms;   // the clamped 128 x 128 form
+static_assert(kCount == kClamped + 1, "one name per configuration");
+using Staged = gemm_f32::GemmCfgF32W<128, 128, 16, 2, 2, 2, true>;
 constexpr int kDefaults[tune::kClasses] = {kByShape, kByShape, kByShape, kByShape};
 const bool kRegistered =
     (tune::register_op(tune::kGemmF32, "gemm_f32", kCount, kNames, kDefaults), true);
@@ -199,29 +230,31 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
   (void)kRegistered;
   const int cls = tune::size_class(tune::kGemmF32, M * N * (K ? K : 1));
   int cfg = tune::get(tune::kGemmF32, cls);
+  const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
+  if (cfg == kClamped) return launch_gemm_c<Staged>(g, s);
   if (cfg >= kByShape) {
-    const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
     const bool strides = lda <= kDirectMaxLd && ldb <= kDirectMaxLd;
     if (cfg > kByShape && strides && N >= kDirect[cfg - kByShape - 1].cols)
       return kDirect[cfg - kByShape - 1].launch(g, s);
-    // The LDS-staged tile, two blocks a CU, is the faster one per unit of K
-    // once several rounds of its 128 x 128 tiles run: 69 ns a round of 256
-    // tiles for one round, 63 for two, 58-60 from four on, 8 more where K is
-    // not a multiple of its stage (guarded loads), against the direct tile's
-    // 67 (4096^3: 945 against 1045 us; but 1536 x 3072 x 2048, whose 288
-    // tiles leave a second round nearly empty: 260 against 171 us in 96 x 64
-    // direct tiles).  It needs rows in whole 16-byte groups; with single
-    // loads it takes 102 ns and is never chosen (3001 x 2777 x 2501: 767
-    // against 389 us).
+    // The LDS-staged 128 x 128 tile, up to three blocks a CU, is the faster
+    // one per unit of K once several rounds of its tiles run: 67 ns a round
+    // of 256 tiles for one round, 63 for two, 58-60 from four on, and 3 us of
+    // ends (4096^3: 941 us against 1044 in direct tiles; 8192 x 8192 x 64: 94
+    // against 115; but 1536 x 3072 x 2048, whose 288 tiles leave a second
+    // round nearly empty: 260 against 171 us in 96 x 64 direct tiles).
     if (strides) {
       double us = 0;
       const DirectForm& d = best_direct(M, N, K, &us);
-      const bool vec = gemm_f32::vec_ok(A, lda, B, ldb) && K % 4 == 0 && N % 4 == 0 && K > 0;
       const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
-      const double ns = 58.0 + 11.0 / (tiles <= 256 ? 1.0 : tiles / 256) + (K % 16 ? 8.0 : 0.0);
-      if (!vec || us <= rounds_us(M, N, K, 128, 128, ns, 3.0)) return d.launch(g, s);
+      const double ns = 58.0 + 9.0 / (tiles <= 256 ? 1.0 : tiles / 256);
+      if (!gemm_f32::clamped_tile<Staged>(g) || us <= rounds_us(M, N, K, 128, 128, ns, 3.0))
+        return d.launch(g, s);
     }
-    cfg = cls < 2 && !strides ? 3 : 9;
+    // whole tiles of aligned rows keep the form without clamps (4096^3: 941
+    // against 956 us)
+    if (!gemm_f32::vec_ok(A, lda, B, ldb) || M % 128 != 0 || N % 128 != 0 || K % 16 != 0)
+      return launch_gemm_c<Staged>(g, s);
+    cfg = 9;
   }
   switch (cfg) {
     case 1: return launch_gemm<GemmCfgF32<256, 128, 16>>(A, lda, B, ldb, Cm, ldc, M, N, K, s);

@@ -31,7 +31,8 @@ FORMS = [(128, 128), (64, 128), (128, 64), (96, 96), (64, 96), (96, 64), (64, 64
 
 @pytest.mark.gpu
 @needs_gpu
-@pytest.mark.parametrize("bm,bn,name", [(m, n, f"d{m}x{n}") for m, n in FORMS])
+@pytest.mark.parametrize("bm,bn,name", [(m, n, f"d{m}x{n}") for m, n in FORMS]
+                         + [(128, 128, "m128n128k16_c")])
 def test_direct_form_edges(bm, bn, name):
     # integers: every sum is exact in FP32 in any order, so equality is asked.
     # The padding beside A's rows and B's columns holds NaN, which must stay out.
