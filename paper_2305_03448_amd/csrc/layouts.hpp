@@ -56,6 +56,14 @@ DESC_HD auto lds_cols(const V& tile, const TY& ty, const TX& tx) {
   return group_by_row<T, kItems>(tile.transpose().template group<kV, 1>()).select(ty).select(tx);
 }
 
+// Transposes of any shape: tile t of n rows (or columns, n >= kV) starts at
+// T t, or at n - kV where fewer than kV would be left; the group of thread x
+// in a tile of h starts at kV x, or at h - kV where it would cross the end.
+template <int T, int kV>
+DESC_HD idx_t tile_start(idx_t t, idx_t n) { return T * t < n - kV ? T * t : n - kV; }
+template <int kV>
+DESC_HD int tile_group(int x, int h) { return kV * x < h - kV ? kV * x : h - kV; }
+
 // Fused split staging (the split-BF16 tile routine reading FP32 operands
 // through buffer windows): a wave stages 16 rows x 8 kChunks values of k of
 // A, lane l taking row l / kChunks of the wave's rows and the octet (8

@@ -22,8 +22,10 @@
 // (block (x, y) takes tile (x + y mod the tiles per row, y)): with the plain
 // order the blocks in flight together write output rows a power-of-two
 // stride apart, which measured 10-13 % slower on MI355X.
-// Tiles on the ragged right or bottom edge (and unaligned matrices) go
-// through a guarded element-by-element copy with the same tile and barrier.
+// Matrices that are not whole tiles of aligned groups take the form at the
+// end of this file (transpose_any_kernel); where a side is shorter than one
+// group, the tiles go through a guarded element-by-element copy with the same
+// tile and barrier.
 // The kernel moves bit patterns only: NaN payloads, signed zeros and
 // subnormals pass unchanged.
 #include "common.hpp"
@@ -128,10 +130,18 @@ __global__ __launch_bounds__(C::block) void transpose32_kernel(const uint32_t* _
   }
 }
 
+template <class E>
+bool any_shape(const void* in, const void* out, int64_t rows, int64_t cols, int T);
+template <class E>
+hipError_t transpose_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
+                         hipStream_t s);
+
 template <class C>
 hipError_t launch_transpose(const uint32_t* in, uint32_t* out, int64_t batch, int64_t rows,
                             int64_t cols, hipStream_t s) {
   constexpr int T = C::t;
+  if (any_shape<uint32_t>(in, out, rows, cols, T))
+    return transpose_any<uint32_t>(in, out, batch, rows, cols, s);
   const dim3 grid((unsigned)((cols + T - 1) / T), (unsigned)((rows + T - 1) / T),
                   (unsigned)batch);
   const bool vec = rows % 4 == 0 && cols % 4 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
@@ -233,10 +243,150 @@ __global__ __launch_bounds__(kBlock) void transpose_elem_kernel(const E* __restr
   }
 }
 
+// ----------------------------------------------------------------- any shape
+// The form for matrices that are not whole tiles of 16-byte groups: odd row
+// lengths, unaligned matrices, ragged edges.  The same tiles, threads and
+// swizzles, with 16-byte accesses at element alignment (the hardware takes
+// them at any address), and edges without element loops:
+//   * a tile that would hold fewer than kV rows or columns starts earlier, so
+//     that it holds kV of them;
+//   * in a tile of hr x hc, a thread's group of kV columns (or, writing, of
+//     kV rows) starts at min(kV x, hc - kV): every access is a whole group
+//     inside the matrix, and two groups may move the same elements twice.
+// Loads are unconditional (rows past the tile read its last row); only the
+// LDS writes and the stores are guarded.
+template <class E, int kT, bool kNt, int kThreads>
+struct AnyShape {
+  static constexpr int v = 16 / (int)sizeof(E), t = kT, block = kThreads;
+  static constexpr int pad = sizeof(E) == 1 ? 4 : sizeof(E) == 4 ? 1 : 0;
+  static constexpr int pitch = kT + pad;
+  static constexpr int tx = kT / v, ty = kThreads / tx, items = kT / ty;
+  static constexpr bool nt = kNt;
+  static_assert(tx * ty == kThreads && ty * items == kT, "tile rows must divide among the threads");
+};
+
+template <class C, class E>
+__global__ __launch_bounds__(C::block) void transpose_any_kernel(const E* __restrict__ in,
+                                                                 E* __restrict__ out,
+                                                                 int64_t rows, int64_t cols) {
+  constexpr int T = C::t, TY = C::ty, TX = C::tx, IT = C::items, V = C::v;
+  typedef E vec_t __attribute__((ext_vector_type(V))) __attribute__((aligned(sizeof(E))));
+  __shared__ __attribute__((aligned(16))) E lds[T * C::pitch];
+  const Block bx{((idx_t)blockIdx.x + (idx_t)blockIdx.y) % (idx_t)gridDim.x, (idx_t)gridDim.x};
+  auto by = block_y();
+  auto thread = thread_x<C::block>();
+  const Block bz{(idx_t)blockIdx.z, (idx_t)gridDim.z};
+  auto tile = [&] {
+    if constexpr (sizeof(E) == 8)
+      return matrix(lds, T, T).template xor_swizzle_by<2, 32, 1>();     // [T][T]
+    else if constexpr (sizeof(E) == 2)
+      return matrix(lds, T, T).template xor_swizzle_by<8, 16, 4>();
+    else
+      return matrix(lds, T, C::pitch).template fst<1>(T);
+  }();
+  auto a = matrices(in, bz.count(), rows, cols).select(bz);
+  auto b = matrices(out, bz.count(), cols, rows).select(bz);
+  const idx_t r0 = layout::tile_start<T, V>(by.index(), rows);
+  const idx_t c0 = layout::tile_start<T, V>(bx.index(), cols);
+  const int hr = (int)(rows - r0 < T ? rows - r0 : T), hc = (int)(cols - c0 < T ? cols - c0 : T);
+  const int y = (int)thread.index() / TX, x = (int)thread.index() % TX;
+
+  vec_t g[IT];
+  const int gc = layout::tile_group<V>(x, hc);          // first column of the thread's group
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int r = y + TY * i;
+    const vec_t* p = (const vec_t*)&a.at(r0 + (r < hr ? r : hr - 1), c0 + gc);
+    if constexpr (C::nt) g[i] = __builtin_nontemporal_load(p);
+    else g[i] = *p;
+  }
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int r = y + TY * i;
+    if (r < hr && V * x < hc) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) tile.at(r, gc + k) = g[i][k];
+    }
+  }
+  sync(thread);
+  const int gr = layout::tile_group<V>(x, hr);          // first row of the thread's group
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int c = y + TY * i;
+    if (c < hc && V * x < hr) {
+      vec_t w;
+#pragma unroll
+      for (int k = 0; k < V; ++k) w[k] = tile.at(gr + k, c);
+      vec_t* p = (vec_t*)&b.at(c0 + c, r0 + gr);
+      if constexpr (C::nt) __builtin_nontemporal_store(w, p);
+      else *p = w;
+    }
+  }
+}
+
+// Whether a call takes that form: anything but whole tiles of T x T in aligned
+// groups, once both sides hold a group.  The element loops it replaces cost
+// 10-15 us a launch by their latency alone: 2000 x 2000 words 17.4 -> 7.1 us,
+// 100 x 200 16-bit elements 16.5 -> 3.2, a batch of 12 1000 x 777 of them
+// 34.9 -> 10.4; and on unaligned matrices most of the time: 8191 x 16001
+// 16-bit elements 360 -> 167 us, 8191 x 8189 words 222 -> 129 us.
+template <class E>
+bool any_shape(const void* in, const void* out, int64_t rows, int64_t cols, int T) {
+  constexpr int kV = 16 / (int)sizeof(E);
+  const bool whole =
+      rows % T == 0 && cols % T == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
+  return !whole && rows >= kV && cols >= kV;
+}
+
+template <class E, int kT, int kThreads, bool kNt>
+hipError_t launch_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
+                      hipStream_t s) {
+  using C = AnyShape<E, kT, kNt, kThreads>;
+  const dim3 grid((unsigned)((cols + kT - 1) / kT), (unsigned)((rows + kT - 1) / kT),
+                  (unsigned)batch);
+  hipLaunchKernelGGL((transpose_any_kernel<C, E>), grid, dim3(kThreads), 0, s, (const E*)in,
+                     (E*)out, rows, cols);
+  return hipGetLastError();
+}
+
+// Tile by size: the largest tile writes the longest pieces of output rows and
+// wins once it fills the GPU; below about 2^20 bytes (2^23 words of 4 bytes)
+// smaller tiles finish sooner (100 x 200 16-bit elements 3.2 against 4.0 us,
+// 500 x 600 words 4.0 against 5.0).  Streaming accesses only where both
+// arrays together outgrow the last-level cache (8192 x 6144 words, 403 MB: 71
+// us against 78; 4112^2 doubles, 271 MB: 70 against 46) and every piece of an
+// output row is whole 128-byte lines: two blocks share a line otherwise, and
+// it must stay in the cache to be written once (16383 x 16381 bytes: 225 us
+// against 197).
+template <class E>
+hipError_t transpose_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
+                         hipStream_t s) {
+  const int64_t count = batch * rows * cols;
+  const bool lines = rows * (int64_t)sizeof(E) % 128 == 0 && (uintptr_t)out % 128 == 0 &&
+                     2 * count * (int64_t)sizeof(E) >= (int64_t)3 << 27;
+  if constexpr (sizeof(E) == 8)
+    return lines ? launch_any<E, 64, 512, true>(in, out, batch, rows, cols, s)
+                 : launch_any<E, 64, 512, false>(in, out, batch, rows, cols, s);
+  if constexpr (sizeof(E) == 4) {
+    if (count < (int64_t)1 << 16)
+      return launch_any<E, 32, 256, false>(in, out, batch, rows, cols, s);
+    if (count < (int64_t)1 << 23)
+      return launch_any<E, 64, 256, false>(in, out, batch, rows, cols, s);
+  } else if constexpr (sizeof(E) < 4) {
+    if (count * (int64_t)sizeof(E) < (int64_t)1 << 20)
+      return launch_any<E, 64, 256, false>(in, out, batch, rows, cols, s);
+  }
+  if constexpr (sizeof(E) <= 4)
+    return lines ? launch_any<E, 128, 512, true>(in, out, batch, rows, cols, s)
+                 : launch_any<E, 128, 512, false>(in, out, batch, rows, cols, s);
+}
+
 template <class E, int kT>
 hipError_t launch_transpose_elem(const void* in, void* out, int64_t batch, int64_t rows,
                                  int64_t cols, hipStream_t s) {
   using C = TransposeCfgE<E, kT>;
+  if (any_shape<E>(in, out, rows, cols, kT))
+    return transpose_any<E>(in, out, batch, rows, cols, s);
   const dim3 grid((unsigned)((cols + kT - 1) / kT), (unsigned)((rows + kT - 1) / kT),
                   (unsigned)batch);
   const bool vec = rows % C::v == 0 && cols % C::v == 0 &&
