@@ -3,7 +3,7 @@
 // barriers in the K loop.
 //
 // A wave holds a (16 FM) x (16 FN) part of C as FM x FN fragments of 16 x 16
-// and takes K in stages of 16.  Lane l = 16 q + c (q = 0..3, c = 0..15)
+// and takes K in stages, of 16 for FP32 products.  Lane l = 16 q + c (q = 0..3, c = 0..15)
 // carries the stage's k = 4 q + kk at step kk, for A and for B alike, so
 //   A : four consecutive k of row m0 + 16 i + c are one 16-byte load, and
 //   B : FN consecutive columns of row k, from n0 + FN c, are one load of
@@ -30,6 +30,7 @@
 #include "common.hpp"
 #include "gemm_f32.hpp"
 #include "layouts.hpp"
+#include "lowp.hpp"
 #include "mfma.hpp"
 #include "view.hpp"
 
@@ -43,7 +44,6 @@ struct DirectCfg {
   static constexpr int threads = 64 * kWM * kWN * kWK;
   static constexpr int wtm = 16 * kFM, wtn = 16 * kFN;       // wave tile
   static constexpr int bm = wtm * kWM, bn = wtn * kWN;       // block tile
-  static constexpr int bk = 16;                              // k per stage
   // the waves' partial tiles, when more than one shares a tile
   static constexpr int lds_floats = kWK > 1 ? kWM * kWN * kWK * wtm * wtn : 4;
   static_assert(kFN >= 1 && kFN <= 4, "one load holds a lane's columns");
@@ -67,9 +67,15 @@ struct Words<1> {
 
 // One tile of C = A * B at block tile (tm, tn).  `lds` holds
 // C::lds_floats floats (unused when one wave takes all of K).
-template <class C>
+//
+// kSplit: the three-product split-BF16 arithmetic.  A stage is then 32 values
+// of K, eight consecutive ones a lane (k = 8 q + kk, two 16-byte loads of a
+// row of A, eight rows of B), split into hi and lo in registers as they are
+// used, for 16 x 16 x 32 bfloat16 instructions on the same lanes.
+template <class C, bool kSplit = false>
 __device__ __forceinline__ void tile(const GemmProblemF32& p, idx_t tm, idx_t tn, float* lds) {
-  constexpr int FM = C::fm, FN = C::fn, WK = C::wk, D = C::depth, BK = C::bk;
+  constexpr int FM = C::fm, FN = C::fn, WK = C::wk, D = C::depth;
+  constexpr int BK = kSplit ? 32 : 16, QK = BK / 4;      // k per stage and per lane
   using awords = typename Words<4>::t;
   using bwords = typename Words<FN>::t;
   auto thread = thread_x<C::threads>();
@@ -90,18 +96,18 @@ __device__ __forceinline__ void tile(const GemmProblemF32& p, idx_t tm, idx_t tn
   const idx_t a_row0 = m0 < p.M ? m0 : p.M - 1;
   const auto a_first = array(&a_g.at(a_row0, 0), p.K);
   const idx_t col = layout::clamped_group<FN>(n0, c16, p.N);
-  uint32_t off_a[FM], off_b[4];
+  uint32_t off_a[FM], off_b[QK];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
     off_a[i] = win_a.row((int32_t)layout::clamped_row(16 * i + c16, p.M - a_row0)) +
                win_a.col_valid(layout::gemm16_frag_k<BK>(quarter));
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
+  for (int kk = 0; kk < QK; ++kk)
     off_b[kk] = win_b.row(layout::gemm16_frag_k<BK>(quarter) + kk) + win_b.col_valid((int32_t)col);
 
   struct Stage {
-    f32x4 a[FM];
-    float b[4][FN];
+    f32x4 a[FM][QK / 4];
+    float b[QK][FN];
   };
   // this wave's whole stages: wk, wk + WK, ... below K / BK
   const idx_t whole = p.K / BK;
@@ -111,9 +117,11 @@ __device__ __forceinline__ void tile(const GemmProblemF32& p, idx_t tm, idx_t tn
     const char* pa = (const char*)&a_first[k0];
     const char* pb = (const char*)&b_g.at(k0, 0);
 #pragma unroll
-    for (int i = 0; i < FM; ++i) s.a[i] = *(const awords*)(pa + off_a[i]);
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+      for (int h = 0; h < QK / 4; ++h) s.a[i][h] = *(const awords*)(pa + off_a[i] + 16 * h);
+#pragma unroll
+    for (int kk = 0; kk < QK; ++kk) {
       const bwords v = *(const bwords*)(pb + off_b[kk]);
       if constexpr (FN == 1) {
         s.b[kk][0] = v;
@@ -129,13 +137,39 @@ __device__ __forceinline__ void tile(const GemmProblemF32& p, idx_t tm, idx_t tn
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto compute = [&](const Stage& s) {
+    if constexpr (kSplit) {
+      // hi and lo of eight values of k, packed for one operand register group
+      auto split8 = [](auto&& value, u32x4& hi, u32x4& lo) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+        for (int e = 0; e < 4; ++e) {
+          const lowp::Split2 p2 = lowp::split_bf16x2(value(2 * e), value(2 * e + 1));
+          hi[e] = p2.hi;
+          lo[e] = p2.lo;
+        }
+      };
+      u32x4 bh[FN], bl[FN];
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+      for (int j = 0; j < FN; ++j) split8([&](int k) { return s.b[k][j]; }, bh[j], bl[j]);
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = mfma::f32_16x16x4(s.a[i][kk], s.b[kk][j], acc[i][j]);
+      for (int i = 0; i < FM; ++i) {
+        u32x4 ah, al;
+        split8([&](int k) { return s.a[i][k / 4][k % 4]; }, ah, al);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          acc[i][j] = mfma::bf16_16x16x32(al, bh[j], acc[i][j]);
+          acc[i][j] = mfma::bf16_16x16x32(ah, bl[j], acc[i][j]);
+          acc[i][j] = mfma::bf16_16x16x32(ah, bh[j], acc[i][j]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = mfma::f32_16x16x4(s.a[i][0][kk], s.b[kk][j], acc[i][j]);
+    }
   };
 
   // D stages in flight: stage it + D is loaded into the registers of stage
@@ -174,10 +208,10 @@ __device__ __forceinline__ void tile(const GemmProblemF32& p, idx_t tm, idx_t tn
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        s.a[i][e] = k + e < left ? *(const float*)(pa + off_a[i] + 4 * e) : 0.f;
+      for (int e = 0; e < QK; ++e)
+        s.a[i][e / 4][e % 4] = k + e < left ? *(const float*)(pa + off_a[i] + 4 * e) : 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < QK; ++kk)
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         s.b[kk][j] = k + kk < left ? *(const float*)(pb + off_b[kk] + 4 * j) : 0.f;

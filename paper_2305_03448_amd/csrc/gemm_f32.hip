@@ -16,6 +16,7 @@
 // and store under guards, so any M, N, K and leading dimensions work.
 //
 // The tile routine is shared with the grouped GEMM (grouped.hip).
+#include "direct_forms.hpp"
 #include "gemm_direct.hpp"
 #include "gemm_f32.hpp"
 #include "launch.hpp"
@@ -107,98 +108,30 @@ hipError_t launch_gemm(const float* A, int64_t lda, const float* B, int64_t ldb,
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ direct tiles
-// gemm_direct.hpp.  What bounds these kernels is the operand traffic through
-// the CU's 32 KB cache: with two blocks on a CU their lines evict each other
-// before the neighbouring lanes and waves have used them (4096^3 in 128 x 128
-// tiles: 1555 us with two blocks a CU, 1045 us with one; 1024 tiles of
-// 64 x 64 at K = 1024: 100 against 84 us).  A long K therefore launches with
-// enough LDS reserved that one block has the CU; with little to read per
-// block the second block's overlap of prologue and stores wins instead
-// (K = 64: 13.2 against 17.2 us), and tiles up to 32 x 32 read too little to
-// disturb each other at any K measured.
-constexpr size_t kOneBlockLds = 84 * 1024;          // over half of a CU's 160 KB
-constexpr int64_t kOneBlockWords = 51200;           // operand words per block from which it pays
-
-template <class C>
-__global__ __launch_bounds__(C::threads) void gemm_direct_kernel(
-    const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
-    float* __restrict__ Cm, int64_t ldc, int64_t M, int64_t N, int64_t K) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  const GemmProblemF32 p{A, lda, B, ldb, Cm, ldc, M, N, K};
-  const auto t = layout::xcd_run_tile(block_x().index(), (M + C::bm - 1) / C::bm,
-                                      (N + C::bn - 1) / C::bn);
-  gemm_direct::tile<C>(p, t.m, t.n, lds);
-}
-
-template <class C>
-hipError_t launch_direct(const GemmProblemF32& g, hipStream_t s) {
-  const int64_t tiles = ((g.M + C::bm - 1) / C::bm) * ((g.N + C::bn - 1) / C::bn);
-  constexpr size_t need = C::lds_floats * sizeof(float);
-  const bool alone = C::bm * C::bn > 32 * 32 && g.K * (C::bm + C::bn) > kOneBlockWords;
-  const size_t bytes = alone && need < kOneBlockLds ? kOneBlockLds : need;
-  hipLaunchKernelGGL((gemm_direct_kernel<C>), dim3((unsigned)tiles), dim3(C::threads), bytes, s,
-                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K);
-  return hipGetLastError();
-}
-
-// The direct forms, smallest tile last.  ns_per_k: measured time a round of
-// 256 tiles (one a CU) takes per unit of K, (t(K = 2048) - t(K = 256)) / 1792.
-// The matrix work of a 128 x 128 tile alone is 53 ns; small tiles pay for
-// their loads instead (16 x 16: 2.1 ns for 0.8 ns of matrix work), but a
-// shape with few tiles is faster in more, smaller ones.
-struct DirectForm {
-  int bm, bn, cols;      // tile; columns one load holds (N must reach them)
-  double ns_per_k;
-  hipError_t (*launch)(const GemmProblemF32&, hipStream_t);
-};
-template <int kFM, int kFN, int kWM, int kWN, int kWK, int kDepth>
-constexpr DirectForm direct(double ns_per_k) {
-  using C = DirectCfg<kFM, kFN, kWM, kWN, kWK, kDepth>;
-  return {C::bm, C::bn, C::fn, ns_per_k, launch_direct<C>};
-}
+// The FP32 direct forms.  The matrix work of a 128 x 128 tile alone is 53 ns;
+// small tiles pay for their loads instead (16 x 16: 2.2 ns for 0.8 ns of
+// matrix work), but a shape with few tiles is faster in more, smaller ones.
 constexpr DirectForm kDirect[] = {
-    direct<4, 4, 2, 2, 1, 3>(67.1),   // 128 x 128
-    direct<4, 4, 1, 2, 2, 2>(36.6),   // 64 x 128
-    direct<4, 4, 2, 1, 2, 2>(38.3),   // 128 x 64
-    direct<3, 3, 2, 2, 1, 3>(42.6),   // 96 x 96
-    direct<4, 3, 1, 2, 2, 3>(27.6),   // 64 x 96
-    direct<3, 4, 2, 1, 2, 3>(27.7),   // 96 x 64
-    direct<4, 4, 1, 1, 4, 2>(18.8),   // 64 x 64
-    direct<3, 4, 1, 1, 4, 4>(13.5),   // 48 x 64
-    direct<4, 3, 1, 1, 4, 4>(13.6),   // 64 x 48
-    direct<3, 3, 1, 1, 4, 4>(10.4),   // 48 x 48
-    direct<2, 4, 1, 1, 4, 4>(9.0),    // 32 x 64
-    direct<4, 2, 1, 1, 4, 4>(10.7),   // 64 x 32
-    direct<2, 2, 1, 1, 4, 6>(5.8),    // 32 x 32
-    direct<1, 4, 1, 1, 4, 4>(4.9),    // 16 x 64
-    direct<4, 1, 1, 1, 4, 4>(8.4),    // 64 x 16
-    direct<1, 2, 1, 1, 8, 6>(4.1),    // 16 x 32
-    direct<2, 1, 1, 1, 8, 6>(4.8),    // 32 x 16
-    direct<1, 1, 1, 1, 16, 4>(2.2),   // 16 x 16
+    direct<false, 4, 4, 2, 2, 1, 3>(67.1),   // 128 x 128
+    direct<false, 4, 4, 1, 2, 2, 2>(36.6),   // 64 x 128
+    direct<false, 4, 4, 2, 1, 2, 2>(38.3),   // 128 x 64
+    direct<false, 3, 3, 2, 2, 1, 3>(42.6),   // 96 x 96
+    direct<false, 4, 3, 1, 2, 2, 3>(27.6),   // 64 x 96
+    direct<false, 3, 4, 2, 1, 2, 3>(27.7),   // 96 x 64
+    direct<false, 4, 4, 1, 1, 4, 2>(18.8),   // 64 x 64
+    direct<false, 3, 4, 1, 1, 4, 4>(13.5),   // 48 x 64
+    direct<false, 4, 3, 1, 1, 4, 4>(13.6),   // 64 x 48
+    direct<false, 3, 3, 1, 1, 4, 4>(10.4),   // 48 x 48
+    direct<false, 2, 4, 1, 1, 4, 4>(9.0),    // 32 x 64
+    direct<false, 4, 2, 1, 1, 4, 4>(10.7),   // 64 x 32
+    direct<false, 2, 2, 1, 1, 4, 6>(5.8),    // 32 x 32
+    direct<false, 1, 4, 1, 1, 4, 4>(4.9),    // 16 x 64
+    direct<false, 4, 1, 1, 1, 4, 4>(8.4),    // 64 x 16
+    direct<false, 1, 2, 1, 1, 8, 6>(4.1),    // 16 x 32
+    direct<false, 2, 1, 1, 1, 8, 6>(4.8),    // 32 x 16
+    direct<false, 1, 1, 1, 1, 16, 4>(2.2),   // 16 x 16
 };
 constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
-
-// A call's time as rounds of 256 tiles, each K steps and the start and end
-// of its tiles: measured at K = 64, 2.0 us a round for 64 x 64 and smaller
-// tiles, 2.5 for 64 x 128, 3.5 for 128 x 128.
-double rounds_us(int64_t M, int64_t N, int64_t K, int bm, int bn, double ns_per_k, double ends) {
-  const double tiles = (double)((M + bm - 1) / bm) * (double)((N + bn - 1) / bn);
-  const double rounds = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
-  return rounds * ((double)K * ns_per_k * 1e-3 + ends);
-}
-
-// The fastest direct form by that estimate (a 16 x 16 tile takes any N).
-const DirectForm& best_direct(int64_t M, int64_t N, int64_t K, double* us) {
-  const DirectForm* best = &kDirect[kDirectForms - 1];
-  *us = 1e300;
-  for (const DirectForm& f : kDirect) {
-    if (N < f.cols) continue;
-    const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, 1.5 + f.bm * f.bn / 8192.0);
-    if (t < *us) { best = &f; *us = t; }
-  }
-  return *best;
-}
 
 // "_rm": the row-major-A tile form; "_w8": eight waves (2 x 4).  "by_shape":
 // a direct form or the LDS-staged 128 x 128 tile, whichever the call's M, N
@@ -244,7 +177,7 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     // round nearly empty: 260 against 171 us in 96 x 64 direct tiles).
     if (strides) {
       double us = 0;
-      const DirectForm& d = best_direct(M, N, K, &us);
+      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
       const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
       const double ns = 58.0 + 9.0 / (tiles <= 256 ? 1.0 : tiles / 256);
       if (!gemm_f32::clamped_tile<Staged>(g) || us <= rounds_us(M, N, K, 128, 128, ns, 3.0))

@@ -21,6 +21,7 @@
 // Padding: Mp, Np are multiples of 256 and Kp a multiple of 128 elements;
 // the pre-pass writes zeros there, so the GEMM main loop has no guards.
 #include "common.hpp"
+#include "direct_forms.hpp"
 #include "gemm_nt.hpp"
 #include "launch.hpp"
 #include "lowp.hpp"
@@ -527,18 +528,62 @@ unsigned grid_for(int64_t items) {
   return (unsigned)(g < 1 ? 1 : g);
 }
 
+// The split-BF16 direct forms (direct_forms.hpp).
+constexpr DirectForm kDirect[] = {
+    direct<true, 4, 4, 2, 2, 1, 1>(41.8),   // 128 x 128
+    direct<true, 4, 4, 1, 2, 2, 1>(20.1),   // 64 x 128
+    direct<true, 4, 4, 2, 1, 2, 1>(20.4),   // 128 x 64
+    direct<true, 4, 4, 1, 1, 4, 1>(10.7),   // 64 x 64
+    direct<true, 3, 3, 1, 1, 4, 2>(9.3),    // 48 x 48
+    direct<true, 2, 4, 1, 1, 4, 2>(7.2),    // 32 x 64
+    direct<true, 2, 2, 1, 1, 4, 3>(6.3),    // 32 x 32
+    direct<true, 1, 4, 1, 1, 4, 2>(4.3),    // 16 x 64
+    direct<true, 1, 2, 1, 1, 8, 3>(3.9),    // 16 x 32
+    direct<true, 2, 1, 1, 1, 8, 3>(4.5),    // 32 x 16
+    direct<true, 1, 1, 1, 1, 16, 2>(2.3),   // 16 x 16
+};
+constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
+
+// Times of the fused forms by the tiles a CU gets (us, K in the formulas per
+// 1000).  128 x 128, two blocks a CU: 35 K for one tile, 50 K for two, 84 K
+// for three, 104 K for four, and 3 us of ends a tile (1000 x 1500 x 777 36 us
+// against 22.5 in 64 x 128 direct tiles; 2048^3 80 against 92).  256 x 256,
+// eight waves: 68 K a round, 88 K when every CU has one, and 11 us of ends
+// (4096^3 366 us against 430 in 128 x 128 tiles, 3001 x 2777 x 2501 201
+// against 214, 2560 x 2560 x 1024 85 against 54).
+double fused128_us(int64_t M, int64_t N, int64_t K) {
+  const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
+  const double each = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
+  const double pairs = (double)(int64_t)(each / 2), odd = each - 2 * pairs;
+  return (pairs * 50.0 + odd * 35.0) * K * 1e-3 + 3.0 * each;
+}
+double fused256_us(int64_t M, int64_t N, int64_t K) {
+  const double tiles = (double)((M + 255) / 256) * (double)((N + 255) / 256);
+  const double rounds = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
+  return rounds * ((68.0 + 20.0 * (tiles < 256 ? tiles / 256 : 1.0)) * K * 1e-3 + 11.0);
+}
+
 // "_w8": eight waves (2 x 4) share the tile instead of four (2 x 2);
 // "_fused": the operands split while they are staged (no pre-pass);
+// "by_shape": a fused or a direct form, whichever the call's M, N and K make
+// faster; "dBMxBN": that direct form (by_shape where a row of C is shorter
+// than one load, or a stride is beyond the direct forms');
 // "_p": fragment reads one group of matrix ops ahead (NtCfg kPipe).
 constexpr const char* kNamesBf16[] = {"m128n128k32", "m256n128k32", "m128n256k32",
                                       "m256n256k32_d1", "m256n256k32_w8d1",
-                                      "m128n128k32_fused", "m256n256k32_w8d1_fused"};
+                                      "m128n128k32_fused", "m256n256k32_w8d1_fused",
+                                      "by_shape", "d128x128", "d64x128", "d128x64", "d64x64",
+                                      "d48x48", "d32x64", "d32x32", "d16x64", "d16x32", "d32x16",
+                                      "d16x16"};
+constexpr int kByShape = 7, kCountBf16 = (int)(sizeof(kNamesBf16) / sizeof(kNamesBf16[0]));
+static_assert(kCountBf16 == kByShape + 1 + kDirectForms, "one name per configuration");
+constexpr int kDefaultsBf16[tune::kClasses] = {kByShape, kByShape, kByShape, kByShape};
 constexpr const char* kNamesFp8[] = {"m128n128k128", "m128n128k64", "m256n128k128",
                                      "m128n256k128", "m256n128k64", "m256n256k64_w8d1",
                                      "m256n256k128_w8d1", "m256n256k128_w8d1_p", "m128n128k128_p"};
 constexpr int kDefaults[tune::kClasses] = {0, 0, 0, 0};
 const bool kRegistered =
-    (tune::register_op(tune::kGemmBf16x3, "gemm_bf16x3", 7, kNamesBf16, kDefaults),
+    (tune::register_op(tune::kGemmBf16x3, "gemm_bf16x3", kCountBf16, kNamesBf16, kDefaultsBf16),
      tune::register_op(tune::kGemmFp8, "gemm_fp8", 9, kNamesFp8, kDefaults), true);
 
 }  // namespace
@@ -598,7 +643,16 @@ hipError_t quant_e4m3_cols(const float* B, int64_t K, int64_t N, int64_t ldb, ui
 hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb, float* Cm,
                        int64_t ldc, int64_t M, int64_t N, int64_t K, void* ws, hipStream_t s) {
   (void)kRegistered;
-  const int cfg = tune::get(tune::kGemmBf16x3, tune::size_class(tune::kGemmBf16x3, M * N * K));
+  int cfg = tune::get(tune::kGemmBf16x3, tune::size_class(tune::kGemmBf16x3, M * N * K));
+  if (cfg >= kByShape && K > 0 && lda <= kDirectMaxLd && ldb <= kDirectMaxLd) {
+    const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
+    if (cfg > kByShape && N >= kDirect[cfg - kByShape - 1].cols)
+      return kDirect[cfg - kByShape - 1].launch(g, s);
+    double us = 0;
+    const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
+    if (us <= fused128_us(M, N, K) && us <= fused256_us(M, N, K)) return d.launch(g, s);
+  }
+  if (cfg >= kByShape) cfg = fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;
   if (cfg >= 5 && K > 0 && lda <= gemm_nt::kSplitMaxLd && ldb <= gemm_nt::kSplitMaxLd) {
     const gemm_nt::F32Operands f{A, lda, B, ldb, M, N, K};
     if (cfg == 6) return launch_split<NtCfg<256, 256, 64, Bf16x3Mode, 1, 2, 4>>(f, Cm, ldc, s);

@@ -212,8 +212,9 @@ constexpr int64_t kSplitMaxLd = int64_t(1) << 24;
 // split, to chunk `octet` of row `row` (A) or BM + column (B^T).
 //   A: octet q is octet q % CPR of row q / CPR.  The 16 rows one wave reads
 //      per octet set are one buffer range (base at the stage's k0), read as
-//      two 16-byte loads per octet when kVec (A 16-byte aligned, lda and K
-//      multiples of 4), else as 8 single loads.
+//      two 16-byte loads per octet (which need 4-byte alignment only); in a
+//      partial stage so only when kVec (A 16-byte aligned, lda and K multiples
+//      of 4), else as 8 single loads.
 //   B: octet q is column q % BN, octet q / BN, which is one octet per wave:
 //      its 8 rows are one buffer range, read as 8 single loads, each
 //      coalesced over the wave's 64 consecutive columns.
@@ -291,7 +292,7 @@ struct SplitSource {
       // k0 < K: the base stays inside the group's first row (or A's)
       const auto rs = buffer_rsrc(&array(a_first[i], p.K).at(k0), win.bytes());
       const uint32_t row = win.row(lr);
-      if constexpr (kVec) {
+      if constexpr (kVec || kFull) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           R.a[i][h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(

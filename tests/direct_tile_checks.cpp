@@ -60,24 +60,25 @@ static bool rows() {
 
 // The stages of kWK waves, the lanes' quarters and steps, and the partial
 // stage with its mask hold every k below K once.
+template <int BK>
 static bool k_split() {
   for (int wk : {1, 2, 4, 8, 16})
     for (idx_t K = 0; K <= 600; ++K) {
       std::vector<int> times(K, 0);
-      const idx_t whole = K / 16;
+      const idx_t whole = K / BK;
       for (int w = 0; w < wk; ++w) {
         const idx_t mine = whole > w ? (whole - w + wk - 1) / wk : 0;
         for (idx_t it = 0; it < mine; ++it)
           for (int q = 0; q < 4; ++q)
-            for (int kk = 0; kk < 4; ++kk) {
-              const idx_t k = (w + it * wk) * 16 + layout::gemm16_frag_k<16>(q) + kk;
+            for (int kk = 0; kk < BK / 4; ++kk) {
+              const idx_t k = (w + it * wk) * BK + layout::gemm16_frag_k<BK>(q) + kk;
               if (k >= K) return false;
               ++times[k];
             }
-        if (K % 16 != 0 && w == (int)(whole % wk))
+        if (K % BK != 0 && w == (int)(whole % wk))
           for (int q = 0; q < 4; ++q)
-            for (int kk = 0; kk < 4; ++kk) {
-              const idx_t k = whole * 16 + layout::gemm16_frag_k<16>(q) + kk;
+            for (int kk = 0; kk < BK / 4; ++kk) {
+              const idx_t k = whole * BK + layout::gemm16_frag_k<BK>(q) + kk;
               if (k < K) ++times[k];
             }
       }
@@ -94,6 +95,6 @@ int main() {
   report("groups_3", groups<3>());
   report("groups_4", groups<4>());
   report("rows", rows());
-  report("k_split", k_split());
+  report("k_split", k_split<16>() && k_split<32>());
   return failures != 0;
 }

@@ -1,4 +1,4 @@
-"""The direct FP32 GEMM tile and the clamped LDS-staged one: their index maps on
+"""The direct GEMM tile (FP32 and split BF16) and the clamped LDS-staged one: their index maps on
 the host, every form on the GPU at the edges of its tiles, and the mixed tiles
 of the grouped GEMM, against exact integer products."""
 import os
@@ -10,7 +10,7 @@ import torch
 
 import paper_2305_03448_amd as desc
 import workloads
-from gpu_util import case, needs_gpu
+from gpu_util import bf16x3_bound, case, needs_gpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2305_03448_amd", "csrc")
@@ -59,6 +59,46 @@ def test_direct_form_edges(bm, bn, name):
             got = buf.cpu().numpy()
             assert np.array_equal(got[:M, :N], want)
             assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+    finally:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, -1)
+
+
+SPLIT_FORMS = [(128, 128), (64, 128), (128, 64), (64, 64), (48, 48), (32, 64), (32, 32), (16, 64),
+               (16, 32), (32, 16), (16, 16)]
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("bm,bn", SPLIT_FORMS)
+def test_direct_split_form_edges(bm, bn):
+    # small integers are bfloat16 values (lo = 0) and their sums exact in FP32:
+    # equality; then N(0, 1) within the mode's a-priori bound
+    op = "gemm_bf16x3"
+    names = [desc.desc_config_name(op, c) for c in range(desc.desc_config_count(op))]
+    try:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, names.index(f"d{bm}x{bn}"))
+        for M, N, K, pad in [(bm, bn, 256, 0), (bm + 1, bn + 1, 33, 3), (bm - 1, bn - 1, 31, 1),
+                             (1, 4, 1, 0), (2 * bm + 5, 3 * bn + 2, 1041, 0), (3, 2, 65, 1)]:
+            case(f"gemm bf16x3 d{bm}x{bn} {M}x{N}x{K} pad {pad}")
+            g = workloads.rng(52)
+
+            def padded(x):
+                t = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), device="cuda")
+                t[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+                return t[:, :x.shape[1]]
+            for normal in (False, True):
+                draw = ((lambda s: g.standard_normal(s).astype(np.float32)) if normal
+                        else (lambda s: g.integers(-4, 5, size=s).astype(np.float32)))
+                A, B = draw((M, K)), draw((K, N))
+                buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
+                desc.desc_gemm(padded(A), padded(B), buf[:M, :N], mode="bf16x3")
+                got = buf.cpu().numpy()
+                assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+                A, B = A.astype(np.float64), B.astype(np.float64)
+                err = np.abs(got[:M, :N] - A @ B)
+                assert (err <= (bf16x3_bound(K) * (np.abs(A) @ np.abs(B)) if normal else 0)).all()
     finally:
         for cls in range(4):
             desc.desc_config_set(op, cls, -1)
