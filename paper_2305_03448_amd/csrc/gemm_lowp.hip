@@ -22,6 +22,8 @@
 // the pre-pass writes zeros there, so the GEMM main loop has no guards.
 #include "common.hpp"
 #include "direct_forms.hpp"
+#include "gemm_direct_nt.hpp"
+#include "gemm_fp8_fused.hpp"
 #include "gemm_nt.hpp"
 #include "launch.hpp"
 #include "lowp.hpp"
@@ -489,6 +491,41 @@ hipError_t launch_nt(const NtOperands& p, int64_t Mp, int64_t Np, hipStream_t s)
   return hipGetLastError();
 }
 
+// One launch from the FP32 operands (gemm_fp8_fused.hpp).
+__global__ __launch_bounds__(64 * gemm_fp8::kFusedWaves) void gemm_fp8_fused_kernel(
+    const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+    float* __restrict__ Cm, int64_t ldc, int64_t M, int64_t N, int64_t K) {
+  __shared__ gemm_fp8::FusedLds lds;
+  constexpr int T = gemm_fp8::kFusedTile;
+  const auto t = layout::xcd_run_tile(block_x().index(), (M + T - 1) / T, (N + T - 1) / T);
+  gemm_fp8::fused_tile(GemmProblemF32{A, lda, B, ldb, Cm, ldc, M, N, K}, t.m, t.n, lds);
+}
+
+hipError_t launch_fp8_fused(const GemmProblemF32& g, hipStream_t s) {
+  constexpr int T = gemm_fp8::kFusedTile;
+  const int64_t tiles = ((g.M + T - 1) / T) * ((g.N + T - 1) / T);
+  hipLaunchKernelGGL(gemm_fp8_fused_kernel, dim3((unsigned)tiles),
+                     dim3(64 * gemm_fp8::kFusedWaves), 0, s, g.A, g.lda, g.B, g.ldb, g.C, g.ldc,
+                     g.M, g.N, g.K);
+  return hipGetLastError();
+}
+
+// The direct tile over the planes (gemm_direct_nt.hpp).
+template <class C>
+__global__ __launch_bounds__(C::threads) void gemm_direct_nt_kernel(NtOperands p) {
+  __shared__ float lds[C::lds_floats];
+  const auto t = layout::xcd_run_tile(block_x().index(), (p.M + C::bm - 1) / C::bm,
+                                      (p.N + C::bn - 1) / C::bn);
+  gemm_nt::direct_tile<C>(p, t.m, t.n, lds);
+}
+
+template <class C>
+hipError_t launch_direct_nt(const NtOperands& p, hipStream_t s) {
+  const int64_t tiles = ((p.M + C::bm - 1) / C::bm) * ((p.N + C::bn - 1) / C::bn);
+  hipLaunchKernelGGL(gemm_direct_nt_kernel<C>, dim3((unsigned)tiles), dim3(C::threads), 0, s, p);
+  return hipGetLastError();
+}
+
 struct LowpLayout {
   int64_t Mp, Np, Kp;
   size_t a_plane, b_plane;       // bytes of one operand plane
@@ -569,6 +606,9 @@ double fused256_us(int64_t M, int64_t N, int64_t K) {
 // faster; "dBMxBN": that direct form (by_shape where a row of C is shorter
 // than one load, or a stride is beyond the direct forms');
 // "_p": fragment reads one group of matrix ops ahead (NtCfg kPipe).
+// "by_shape" (FP8): one of the forms below by the rule of fp8_by_shape;
+// "fused32x32": one launch from the FP32 operands; "d32x32", "d64x64": direct
+// tiles over the planes.
 constexpr const char* kNamesBf16[] = {"m128n128k32", "m256n128k32", "m128n256k32",
                                       "m256n256k32_d1", "m256n256k32_w8d1",
                                       "m128n128k32_fused", "m256n256k32_w8d1_fused",
@@ -580,11 +620,36 @@ static_assert(kCountBf16 == kByShape + 1 + kDirectForms, "one name per configura
 constexpr int kDefaultsBf16[tune::kClasses] = {kByShape, kByShape, kByShape, kByShape};
 constexpr const char* kNamesFp8[] = {"m128n128k128", "m128n128k64", "m256n128k128",
                                      "m128n256k128", "m256n128k64", "m256n256k64_w8d1",
-                                     "m256n256k128_w8d1", "m256n256k128_w8d1_p", "m128n128k128_p"};
+                                     "m256n256k128_w8d1", "m256n256k128_w8d1_p", "m128n128k128_p",
+                                     "by_shape", "fused32x32", "d32x32", "d64x64"};
+constexpr int kFp8ByShape = 9, kCountFp8 = (int)(sizeof(kNamesFp8) / sizeof(kNamesFp8[0]));
+constexpr int kDefaultsFp8[tune::kClasses] = {kFp8ByShape, kFp8ByShape, kFp8ByShape, kFp8ByShape};
 constexpr int kDefaults[tune::kClasses] = {0, 0, 0, 0};
+constexpr int kFp8Fused = 10, kFp8D64 = 12;
+using Fp8D32 = DirectNtCfg<1, 1, 16, 2>;
+using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;
+
+// The FP8 form of a call.  With up to 256 tiles of 32 x 32 (one a CU) and K in
+// the registers of one block, or 512 tiles and half that K, the one-launch
+// form saves two launches (512^3 10.0 against 17.4 us, 700 x 700 x 300 16.5
+// against 20.9; beyond, its repeated operand reads cost more than they: 1024 x
+// 1024 x 512 32 against 17).  With up to 256 tiles of 32 x 32, then of 64 x 64,
+// the direct tiles share K among 16 or 8 waves (64 x 64 x 4096 22 against 36
+// us, 128 x 2048 x 2048 20.5 against 27, 1024 x 1024 x 4096 34 against 37).
+// Beyond that the LDS-staged tiles, by M N K.
+int fp8_by_shape(int64_t M, int64_t N, int64_t K, int cls) {
+  auto tiles = [&](int64_t t) { return (double)((M + t - 1) / t) * (double)((N + t - 1) / t); };
+  constexpr int64_t kOnce = gemm_fp8::kFusedWaves * gemm_fp8::kFusedStep;
+  if ((tiles(32) <= 256 && K <= kOnce) || (tiles(32) <= 512 && K <= kOnce / 2)) return kFp8Fused;
+  if (tiles(32) <= 256) return kFp8Fused + 1;
+  if (tiles(64) <= 256) return kFp8D64;
+  constexpr int kStaged[tune::kClasses] = {1, 0, 8, 7};
+  return kStaged[cls];
+}
+
 const bool kRegistered =
     (tune::register_op(tune::kGemmBf16x3, "gemm_bf16x3", kCountBf16, kNamesBf16, kDefaultsBf16),
-     tune::register_op(tune::kGemmFp8, "gemm_fp8", 9, kNamesFp8, kDefaults), true);
+     tune::register_op(tune::kGemmFp8, "gemm_fp8", kCountFp8, kNamesFp8, kDefaultsFp8), true);
 
 }  // namespace
 
@@ -684,6 +749,11 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
 hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, float* Cm,
                     int64_t ldc, int64_t M, int64_t N, int64_t K, void* ws, hipStream_t s) {
   (void)kRegistered;
+  const int cls = tune::size_class(tune::kGemmFp8, M * N * K);
+  int cfg = tune::get(tune::kGemmFp8, cls);
+  if (cfg == kFp8ByShape) cfg = fp8_by_shape(M, N, K, cls);
+  if (cfg == kFp8Fused && K > 0 && lda <= gemm_fp8::kFusedMaxLd && ldb <= gemm_fp8::kFusedMaxLd)
+    return launch_fp8_fused(GemmProblemF32{A, lda, B, ldb, Cm, ldc, M, N, K}, s);
   const LowpLayout L = lowp_layout(2, M, N, K);
   uint8_t* w = (uint8_t*)ws;
   uint8_t *qa = w + L.off[0], *qb = w + L.off[2];
@@ -698,7 +768,12 @@ hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     go(B, K, N, ldb, (const float*)part, S, L.Np, qb, L.Np, L.Kp, L.Kp, sb, vin, true);
   });
   NtOperands p{{qa, nullptr}, {qb, nullptr}, L.Kp, Cm, ldc, M, N, sa, sb};
-  switch (tune::get(tune::kGemmFp8, tune::size_class(tune::kGemmFp8, M * N * K))) {
+  if (cfg >= kFp8Fused) {
+    if (cfg == kFp8D64 && gemm_nt::direct_tile_ok<Fp8D64>(L.Kp))
+      return launch_direct_nt<Fp8D64>(p, s);
+    if (gemm_nt::direct_tile_ok<Fp8D32>(L.Kp)) return launch_direct_nt<Fp8D32>(p, s);
+  }
+  switch (cfg) {
     case 1: return launch_nt<NtCfg<128, 128, 64, Fp8Mode>>(p, L.Mp, L.Np, s);
     case 2: return launch_nt<NtCfg<256, 128, 128, Fp8Mode>>(p, L.Mp, L.Np, s);
     case 3: return launch_nt<NtCfg<128, 256, 128, Fp8Mode>>(p, L.Mp, L.Np, s);

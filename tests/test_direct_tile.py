@@ -140,3 +140,54 @@ def test_grouped_mixed_tiles(count):
         got = buf.cpu().numpy()
         assert np.array_equal(got[:M, :N], w), (M, N, K)
         assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("name,t", [("fused32x32", 32), ("d32x32", 32), ("d64x64", 64),
+                                    ("by_shape", 32)])
+def test_fp8_small_forms(name, t):
+    # e4m3 values 448 / 2^i with 448 in every row and column: unit scales, and
+    # products and sums that are exact in the instruction and in FP32
+    op = "gemm_fp8"
+    names = [desc.desc_config_name(op, c) for c in range(desc.desc_config_count(op))]
+
+    def padded(x, pad):
+        b = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), device="cuda")
+        b[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+        return b[:, :x.shape[1]]
+    try:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, names.index(name))
+        for M, N, K, pad in [(t, t, 64, 0), (t + 1, t - 1, 65, 3), (1, 1, 1, 0), (3 * t + 5, 2, 63, 1),
+                             (2 * t, 5 * t + 3, 1024, 0), (t - 1, 2 * t + 7, 1025, 2),
+                             (40, 70, 2500, 1), (7, 5, 0, 0), (600, 900, 130, 0)]:
+            case(f"gemm fp8 {name} {M}x{N}x{K} pad {pad}")
+            g = workloads.rng(53)
+            A, B = (np.float32(448) * (g.integers(-1, 2, size=s) / 2.0 ** g.integers(0, 3, size=s))
+                    .astype(np.float32) for s in ((M, K), (K, N)))
+            if K:
+                A[:, K // 2] = 448
+                B[K // 2, :] = 448
+            buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
+            desc.desc_gemm(padded(A, pad), padded(B, pad), buf[:M, :N], mode="fp8")
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[:M, :N], (A.astype(np.float64) @ B.astype(np.float64))
+                                  .astype(np.float32))
+            assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+        # magnitudes whose scale overflows, zero rows, infinities and NaN: the
+        # same bits as the plane form (K = 40 is one instruction a tile)
+        A, B = (g.standard_normal(s).astype(np.float32) for s in ((70, 40), (40, 50)))
+        A[3] *= np.float32(1e-38); A[5] = 0; A[7, 2] = np.inf; A[9, 1] = np.nan; B[:, 4] = 0
+        B[:, 6] *= np.float32(1e-39); B[5, 8] = -np.inf
+        out = []
+        for cfg in (name, "m128n128k128"):
+            for cls in range(4):
+                desc.desc_config_set(op, cls, names.index(cfg))
+            C = torch.empty((70, 50), device="cuda")
+            desc.desc_gemm(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), C, mode="fp8")
+            out.append(C.cpu().numpy())
+        assert np.array_equal(out[0], out[1], equal_nan=True)
+    finally:
+        for cls in range(4):
+            desc.desc_config_set(op, cls, -1)
