@@ -404,11 +404,13 @@ desc_status desc_scan_batched_i32(const int32_t* in, int32_t* out, int64_t batch
  *   reduce : out[s] = exact int64 sum of segment s (0 for an empty segment).
  *   scan   : out[i] = in[offsets[s]] + ... + in[i] modulo 2^32 for i in
  *            segment s; positions outside every segment are not written.
- * The reduce of up to 8192 segments runs as one persistent launch (every
- * block plans the units of all segments in its LDS and then takes every
- * G-th unit, G the blocks that fit the device at once; no block waits for
- * another before the end of the call); the scan, a larger reduce and the
- * batched forms run as a one-block planning kernel and one main kernel.
+ * The reduce of up to 8192 segments, unless they are many (from 2048) and
+ * short on average (up to 32768 elements), runs as one persistent launch
+ * (every block plans the units of all segments in its LDS and then takes a
+ * contiguous range of units, G ranges for the G blocks that fit the device
+ * at once; a block waits only for the tail sums of blocks before it); the
+ * scan, every other reduce and the batched forms run as a one-block planning
+ * kernel and one main kernel.
  * All state lives in the workspace, so every form may be captured in a HIP
  * graph and replayed.  The workspace is zeroed once before its first use
  * (its header holds the device status word, the wait limit and the

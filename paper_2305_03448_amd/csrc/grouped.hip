@@ -25,6 +25,7 @@
 #include "tuning.hpp"
 #include "view.hpp"
 #include "wave.hpp"
+#include "wave_search.hpp"
 
 #include "../../include/desc.h"
 
@@ -83,26 +84,6 @@ __device__ __forceinline__ int64_t block_excl(int64_t v, int64_t* excl, int64_t*
   sync(thread);
   *excl = before + incl - v;
   return tot;
-}
-
-// Last i in [0, G) with start[i] <= t, for a nondecreasing start with
-// start[0] <= t < start[G]: a 64-way search by one whole wave.  Each round
-// every lane reads one boundary and a ballot counts those <= t (a prefix of
-// the lanes), so G = 512 takes two rounds of parallel loads instead of nine
-// dependent ones.
-template <class T>
-__device__ __forceinline__ idx_t wave_owner(const T* start, int64_t G, int64_t t) {
-  auto st = array(start, G);
-  const idx_t lane = lane_of_wave().index();
-  idx_t lo = 0, hi = G;
-  while (hi - lo > 1) {
-    const idx_t step = (hi - lo + kWave - 1) / kWave;
-    const idx_t i = lo + lane * step;
-    const bool le = i < hi && st[i] <= t;
-    lo += ((idx_t)__popcll(__ballot(le)) - 1) * step;
-    hi = lo + step < hi ? lo + step : hi;
-  }
-  return lo;
 }
 
 // Sort key of the planned order: 0 .. kKBuckets-1 for large-tile problems,

@@ -153,14 +153,19 @@ struct SegUnit {
   idx_t seg, j, begin, len;   // segment, unit index inside it, first position, length
   bool single;                // the segment has one unit only
 };
+// Unit u, known to belong to segment s.
 template <class VO, class VU>
-DESC_HD SegUnit seg_unit(const VO& off, const VU& unit_start, int64_t n, int64_t S, int64_t unit,
-                         int64_t u) {
-  const idx_t s = seg_of_unit(unit_start, S, u);
+DESC_HD SegUnit seg_unit_of(const VO& off, const VU& unit_start, int64_t n, int64_t unit,
+                            int64_t u, idx_t s) {
   const idx_t j = u - unit_start[s];
   const idx_t b = seg_clamp(off[s], n) + j * unit;
   const idx_t e = seg_clamp(off[s + 1], n);
   return SegUnit{s, j, b, (e - b) < unit ? (e - b) : unit, (unit_start[s + 1] - unit_start[s]) == 1};
+}
+template <class VO, class VU>
+DESC_HD SegUnit seg_unit(const VO& off, const VU& unit_start, int64_t n, int64_t S, int64_t unit,
+                         int64_t u) {
+  return seg_unit_of(off, unit_start, n, unit, u, seg_of_unit(unit_start, S, u));
 }
 
 // Decoupled look-back over the earlier units of a segment: at window w a

@@ -4,7 +4,8 @@
 //
 // Work is cut into units: segment s of length L_s gives ceil(L_s / UNIT)
 // units of at most UNIT consecutive elements (an empty segment gives none);
-// UNIT is 8K to 64K elements, picked per size class by the tuning table.
+// UNIT is 8K to 64K elements, picked per size class by the tuning table or from
+// the mean segment length (below).
 // A unit finds its segment by binary search over the exclusive prefix of the
 // unit counts, loads its elements with dword-aligned 16-byte loads (segments
 // start anywhere), and
@@ -15,8 +16,8 @@
 //           stopped at the segment's first unit), and writes its part of the
 //           segment's scan.
 //
-// Reduce, up to kSegLds segments (the batched workloads: thousands of
-// uneven segments): one persistent launch.  Every block computes the unit
+// Reduce, up to kSegLds segments (unless there are many short ones, below): one
+// persistent launch.  Every block computes the unit
 // prefix into its LDS (S + 1 int32) and then walks its own contiguous range
 // of units in order, keeping running sums per segment, so it streams through
 // contiguous memory and synchronises only where a segment ends.  A segment
@@ -28,13 +29,14 @@
 // advances the generation, as the plain scan does, so no word older than
 // the previous call can match a later tag.
 //
-// Scan (and the reduce above kSegLds segments, and the batched forms): a
+// Scan (and the other reduces, and the batched forms): a
 // one-block plan kernel writes the unit prefix to the workspace (zeroing
 // the reduce outputs of segments without exactly one unit, which the units
 // then add to atomically; clearing the scan status words), and a main
 // kernel runs one block per unit (launched for the bound S + n / UNIT units;
 // blocks past the total return at once, and units are handed out in block
 // order, so a unit waits only on units whose blocks are already running).
+// With many short segments a block of that kernel takes one unit per wave.
 //
 // Integer addition is associative, so results are exact and independent of
 // the order.
@@ -45,6 +47,7 @@
 #include "tuning.hpp"
 #include "view.hpp"
 #include "wave.hpp"
+#include "wave_search.hpp"
 
 namespace desc {
 namespace {
@@ -151,7 +154,10 @@ struct UnitInfo {
   bool single;                // the segment has one unit only
 };
 
-// Unit u of this block (layout::seg_unit, read by thread 0 and shared).
+// Unit u of this block (layout::seg_unit, found by wave 0 and shared).  The
+// 64-way search takes two or three rounds of parallel loads where one
+// thread's binary search took a dependent load per step, 14 of them (8 us a
+// block) at 16384 segments.
 template <class C>
 __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t* unit_start,
                                           int64_t n, int64_t S, int64_t total, UnitInfo* out) {
@@ -159,39 +165,27 @@ __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t*
   auto thread = thread_x<C::block>();
   const idx_t u = block_x().index();
   if (u >= total) return false;
-  if (thread.index() == 0) {
+  if (thread.index() < kWave) {
     const layout::SegUnit su =
-        layout::seg_unit(array(offsets, S + 1), array(unit_start, S + 1), n, S, C::unit, u);
-    s_info[0] = su.seg; s_info[1] = su.j; s_info[2] = su.begin;
-    s_info[3] = su.len; s_info[4] = su.single;
+        layout::seg_unit_of(array(offsets, S + 1), array(unit_start, S + 1), n, C::unit, u,
+                            wave_owner(unit_start, S, u));
+    if (thread.index() == 0) {
+      s_info[0] = su.seg; s_info[1] = su.j; s_info[2] = su.begin;
+      s_info[3] = su.len; s_info[4] = su.single;
+    }
   }
   sync(thread);
   *out = UnitInfo{s_info[0], s_info[1], s_info[2], s_info[3], s_info[4] != 0};
   return true;
 }
 
-// Unit u from a unit prefix kept in LDS (int32, S + 1 entries): read by
-// thread 0 and shared; the caller synchronises before the next unit.
-template <class C>
-__device__ __forceinline__ UnitInfo unit_info_lds(const int64_t* offsets, const int32_t* s_us,
-                                                 int64_t n, int64_t S, idx_t u) {
-  __shared__ int64_t s_info[5];
-  auto thread = thread_x<C::block>();
-  if (thread.index() == 0) {
-    const layout::SegUnit su =
-        layout::seg_unit(array(offsets, S + 1), array(s_us, S + 1), n, S, C::unit, u);
-    s_info[0] = su.seg; s_info[1] = su.j; s_info[2] = su.begin;
-    s_info[3] = su.len; s_info[4] = su.single;
-  }
-  sync(thread);
-  return UnitInfo{s_info[0], s_info[1], s_info[2], s_info[3], s_info[4] != 0};
-}
-
 // Every block's plan for the persistent forms: s_us[s] = units before
 // segment s (exclusive prefix of the unit counts), s_us[S] = the total.
 // The counts are computed with strided, independent loads of the offsets
 // (in flight together), then thread t scans ceil(S / kThreads) consecutive
-// counts in LDS.
+// counts in LDS, made odd so that the lanes' counts lie in different banks
+// (at 8000 segments 256 threads would be 32 words apart, all in one: the plan
+// took 50 of the 74 us of a reduce of 8.6 M elements).
 template <int kThreads>
 __device__ __forceinline__ int32_t lds_unit_plan(const int64_t* offsets, int64_t n, int64_t S,
                                                  int64_t unit, int32_t* s_us, int32_t* s_wsum) {
@@ -205,7 +199,7 @@ __device__ __forceinline__ int32_t lds_unit_plan(const int64_t* offsets, int64_t
     us[s] = (int32_t)layout::seg_units(len, unit);
   }
   sync(thread);
-  const idx_t per = (S + kThreads - 1) / kThreads;
+  const idx_t per = ((S + kThreads - 1) / kThreads) | 1;
   const idx_t s0 = thread.index() * per, s1 = s0 + per < S ? s0 + per : S;
   int32_t mine = 0;
   for (idx_t s = s0; s < s1; ++s) mine += us[s];
@@ -233,6 +227,43 @@ __device__ __forceinline__ int32_t lds_unit_plan(const int64_t* offsets, int64_t
   return total;
 }
 
+// First element of round r of the wave of thread t (a uniform value).
+template <class C>
+__device__ __forceinline__ idx_t round_start(uint32_t t, int r) {
+  return ((idx_t)__builtin_amdgcn_readfirstlane(t / kWave) * C::rounds + r) * 256;
+}
+
+// Elements at .. at + 3 of a run of len >= 4 elements, 0 past its end, by one
+// unconditional 16-byte load: a group of four that would cross the end starts
+// at the last four elements instead, whose first words belong to earlier
+// groups and are dropped (with every word guarded, 16384 segments of 1000
+// elements on average took 268 us to scan).
+template <bool kNt>
+__device__ __forceinline__ void load_group(const int32_t* run, int at, int len, uint32_t (&x)[4]) {
+  const int from = at < len - 4 ? at : len - 4;
+  const i32x4u* p = (const i32x4u*)(run + from);
+  i32x4u q;
+  if constexpr (kNt) q = __builtin_nontemporal_load(p);
+  else q = *p;
+  const int d = at - from;   // 0 but for the group that crosses the end and those past it
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t v = (uint32_t)q[k];
+    if (k < 3) v = d == 1 ? (uint32_t)q[k + 1] : v;
+    if (k < 2) v = d == 2 ? (uint32_t)q[k + 2] : v;
+    if (k < 1) v = d == 3 ? (uint32_t)q[k + 3] : v;
+    x[k] = at + k < len ? v : 0u;
+  }
+}
+// The up to three elements of a shorter run: thread 0's.
+__device__ __forceinline__ void load_tiny(const int32_t* run, int len, bool first,
+                                          uint32_t (&x)[4]) {
+  if (!first) return;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (k < len) x[k] = (uint32_t)run[k];
+}
+
 // The unit's elements as [waves][rounds][lanes][4]; x[r][k] gets element
 // (w * rounds + r) * 256 + lane * 4 + k (0 beyond the unit's length).
 // kNt: non-temporal 16-byte loads (the reduce, which only streams its input;
@@ -257,13 +288,20 @@ __device__ __forceinline__ void load_unit(const int32_t* in, const UnitInfo& ui,
       x[r][2] = (uint32_t)q.z; x[r][3] = (uint32_t)q.w;
     }
   } else {
-    auto mine = layout::wave_striped<kWaves, kRounds>(array(&unit[0], kUnit).group<4>(), 0, wv,
-                                                      lane);
+    // a partial unit; a wave whose rounds all lie past the end loads nothing
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      auto g = mine.idx(r);
+    for (int r = 0; r < kRounds; ++r)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) x[r][k] = g.pos(k) < ui.len ? (uint32_t)g[k] : 0u;
+      for (int k = 0; k < 4; ++k) x[r][k] = 0u;
+    const int len = (int)ui.len;
+    if (len < 4) {
+      load_tiny(&unit[0], len, t == 0, x[0]);
+    } else if (round_start<C>(t, 0) < ui.len) {
+      auto mine = layout::wave_striped<kWaves, kRounds>(array(&unit[0], kUnit).group<4>(), 0, wv,
+                                                        lane);
+#pragma unroll
+      for (int r = 0; r < kRounds; ++r)
+        load_group<kNt>(&unit[0], (int)mine.idx(r).pos(0), len, x[r]);
     }
   }
 }
@@ -536,15 +574,25 @@ __device__ __forceinline__ void scan_unit(const int32_t* __restrict__ in,
       q.z = (int32_t)(x[r][2] + add); q.w = (int32_t)(x[r][3] + add);
       mine[r] = q;
     }
-  } else {
+  } else {                                   // as the loads of a partial unit
+    auto vec = layout::wave_striped<kWaves, kRounds>(array((i32x4u*)&unit[0], kUnit / 4), 0, owv,
+                                                     olane);
     auto mine = layout::wave_striped<kWaves, kRounds>(array(&unit[0], kUnit).group<4>(), 0,
                                                       owv, olane);
+    const idx_t left = ui.len - round_start<C>(ot, 0);
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-      auto g = mine.idx(r);
+      if (256 * (r + 1) <= left) {
+        i32x4u q;
+        q.x = (int32_t)(x[r][0] + add); q.y = (int32_t)(x[r][1] + add);
+        q.z = (int32_t)(x[r][2] + add); q.w = (int32_t)(x[r][3] + add);
+        vec[r] = q;
+      } else if (256 * r < left) {
+        auto g = mine.idx(r);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (g.pos(k) < ui.len) g[k] = (int32_t)(x[r][k] + add);
+        for (int k = 0; k < 4; ++k)
+          if (g.pos(k) < ui.len) g[k] = (int32_t)(x[r][k] + add);
+      }
     }
   }
 }
@@ -565,6 +613,143 @@ __global__ __launch_bounds__(C::block) void seg_scan_kernel(const int32_t* __res
                max_polls(__hip_atomic_load(&hdr->wait_limit, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT)),
                hdr, sh);
+}
+
+// --------------------------------------------------------------------------
+// Many short segments.  With a block per unit, a segment of tens of elements
+// still costs a block its chain of loads (total, search, offsets, values:
+// about 4 us with 8 blocks a CU, 50-60 us for 16384 segments).  Here a block
+// takes one unit per wave: the waves look their units up side by side, each
+// wave whose unit is a whole segment of at most kShortLen elements reduces or
+// scans it alone, and then the block works through its other units in order,
+// as a block per unit would.
+constexpr int kShortRounds = 4;
+constexpr int kShortLen = 256 * kShortRounds;
+
+// A short segment's values: round r of lane l holds elements 256 r + 4 l ...
+__device__ __forceinline__ void load_short(const int32_t* in, idx_t begin, int len,
+                                           uint32_t (&x)[kShortRounds][4]) {
+  auto run = array(in, 0).snd(begin);
+  auto mine = layout::wave_striped<1, kShortRounds>(array(&run[0], kShortLen).group<4>(), 0,
+                                                    Wave<1>{0, 1}, lane_of_wave());
+#pragma unroll
+  for (int r = 0; r < kShortRounds; ++r)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[r][k] = 0u;
+  if (len < 4) {
+    load_tiny(&run[0], len, lane_of_wave().index() == 0, x[0]);
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < kShortRounds; ++r)
+    if (256 * r < len) load_group<false>(&run[0], (int)mine.idx(r).pos(0), len, x[r]);
+}
+
+// This block's units, one per wave, in LDS.
+template <class C>
+struct BlockUnits {
+  UnitInfo ui[C::waves];
+  int count;
+};
+__device__ __forceinline__ bool is_short(const UnitInfo& ui) {
+  return ui.single && ui.len <= kShortLen;
+}
+template <class C>
+__device__ __forceinline__ void find_units(const int64_t* offsets, const int64_t* unit_start,
+                                           int64_t n, int64_t S, int64_t total,
+                                           BlockUnits<C>& bu) {
+  auto thread = thread_x<C::block>();
+  const int w = (int)wave_of_block<C::block>().index();
+  const idx_t u0 = block_x().index() * C::waves, u = u0 + w;
+  if (u < total) {
+    const layout::SegUnit su =
+        layout::seg_unit_of(array(offsets, S + 1), array(unit_start, S + 1), n, C::unit, u,
+                            wave_owner(unit_start, S, u));
+    if (lane_of_wave().index() == 0)
+      bu.ui[w] = UnitInfo{su.seg, su.j, su.begin, su.len, su.single};
+  }
+  if (thread.index() == 0) bu.count = total - u0 < C::waves ? (int)(total - u0) : C::waves;
+  sync(thread);
+}
+
+template <class C>
+__global__ __launch_bounds__(C::block) void seg_reduce_short_kernel(
+    const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ offsets, int64_t S,
+    const int64_t* __restrict__ total, const int64_t* __restrict__ unit_start,
+    int64_t* __restrict__ out) {
+  __shared__ BlockUnits<C> bu;
+  __shared__ int64_t s_w[C::waves];
+  if (block_x().index() * C::waves >= total[0]) return;
+  find_units<C>(offsets, unit_start, n, S, total[0], bu);
+  auto thread = thread_x<C::block>();
+  auto o = array(out, S);
+  const int w = (int)wave_of_block<C::block>().index();
+  if (w < bu.count && is_short(bu.ui[w])) {
+    uint32_t x[kShortRounds][4];
+    load_short(in, bu.ui[w].begin, (int)bu.ui[w].len, x);
+    int64_t acc = 0;
+#pragma unroll
+    for (int r = 0; r < kShortRounds; ++r)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc += (int64_t)(int32_t)x[r][k];
+    acc = wave::sum_i64(acc);
+    if (lane_of_wave().index() == 0) o[bu.ui[w].seg] = acc;
+  }
+#pragma clang loop unroll(disable)
+  for (int i = 0; i < bu.count; ++i) {
+    if (is_short(bu.ui[i])) continue;
+    const int64_t t = reduce_unit<C>(in, bu.ui[i], s_w);
+    if (thread.index() == 0) {
+      if (bu.ui[i].single) o[bu.ui[i].seg] = t;
+      else __hip_atomic_fetch_add(&o[bu.ui[i].seg], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    sync(thread);                          // s_w is reused by the next unit
+  }
+}
+
+template <class C>
+__global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
+    const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
+    const int64_t* __restrict__ offsets, int64_t S, const int64_t* __restrict__ total,
+    const int64_t* __restrict__ unit_start, uint64_t* __restrict__ status,
+    WsHeader* __restrict__ hdr) {
+  __shared__ BlockUnits<C> bu;
+  __shared__ ScanShared sh;
+  const idx_t u0 = block_x().index() * C::waves;
+  if (u0 >= total[0]) return;
+  find_units<C>(offsets, unit_start, n, S, total[0], bu);
+  auto thread = thread_x<C::block>();
+  const int w = (int)wave_of_block<C::block>().index();
+  if (w < bu.count && is_short(bu.ui[w])) {   // whole segments: nothing to publish or look up
+    const idx_t len = bu.ui[w].len;
+    uint32_t x[kShortRounds][4];
+    load_short(in, bu.ui[w].begin, (int)len, x);
+    auto run = array(out, 0).snd(bu.ui[w].begin);
+    auto mine = layout::wave_striped<1, kShortRounds>(array(&run[0], kShortLen).template group<4>(),
+                                                      0, Wave<1>{0, 1}, lane_of_wave());
+    uint32_t carry = 0;
+#pragma unroll
+    for (int r = 0; r < kShortRounds; ++r) {
+      x[r][1] += x[r][0];
+      x[r][2] += x[r][1];
+      x[r][3] += x[r][2];
+      const uint32_t incl = wave::inclusive_add_u32(x[r][3]);
+      const uint32_t ex = carry + incl - x[r][3];
+      auto g = mine.idx(r);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (g.pos(k) < len) g[k] = (int32_t)(x[r][k] + ex);
+      carry += wave::lane_read_u32(incl, kWave - 1);
+    }
+  }
+  const uint32_t polls = max_polls(
+      __hip_atomic_load(&hdr->wait_limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma clang loop unroll(disable)
+  for (int i = 0; i < bu.count; ++i) {
+    if (is_short(bu.ui[i])) continue;
+    scan_unit<C>(in, out, bu.ui[i], u0 + i, status, polls, hdr, sh);
+    sync(thread);                          // sh is reused by the next unit
+  }
 }
 
 // Upper bound on the units of any configuration (the smallest unit).
@@ -600,12 +785,50 @@ bool persistent_fits(int64_t n, int64_t S) {
   return S > 0 && S <= kSegLds && max_units(n, S) < (1ll << 31);
 }
 
+// Whether a call takes the form for many short segments (lengths log-uniform,
+// so that half of them are far below the mean; us, one unit per block or the
+// persistent reduce / this form):
+//   reduce, mean length   380: 4000 segments 19 / 13, 8192: 33 / 20, 16384: 51 / 32
+//                        2900: 4000 segments 24 / 20, 8192: 42 / 33, 16384: 73 / 56
+//                         23K: 2048 segments 42 / 40, 8192: 145 / 131, 16384: 273 / 257
+//     and below 2000 segments within 1 us either way; of 74K, where the
+//     persistent reduce is as fast (8192: 371 / 367) and a block per unit is
+//     not (9000: 435 / 410);
+//   scan, mean length     380: 4000 segments 18 / 16, 8192: 31 / 24, 16384: 57 / 38
+//                        1080: 16384 segments 61 / 48
+//                        2900: 4000 segments 27 / 37, 16384: 99 / 112, since the
+//     units of a long segment in one block follow each other where separate
+//     blocks overlap them, and 10 / 14 already at 1024 segments of 380.
+constexpr int64_t kShortCount = 2048, kShortReduceMean = 32768, kShortScanMean = 1536;
+bool short_reduce(int64_t n, int64_t S, bool persistent) {
+  return S >= kShortCount && (n <= kShortReduceMean * S || !persistent);
+}
+bool short_scan(int64_t n, int64_t S) { return S >= kShortCount && n <= kShortScanMean * S; }
+
+// Unit size by mean length ("by_mean"; us, units of 8K / 16K / 32K): a unit
+// shorter than the segments splits them into more units to look back over,
+// a longer one leaves most of a block idle on the segments it covers.
+//   reduce  16384 segments of 2900 on average: 73 / 106 / 221; 8192 of 23K:
+//           145 / 143 / 163; 4096 of 76K (persistent): 208 / 206 / 195; 9000
+//           of 74K (a wave's unit each): 430 / 410 / 463
+//   scan    16384 of 8.7K: 226 / 231 / 319; 8192 of 23K: 301 / 288 / 299;
+//           1000 of 78K: 148 / 131 / 125; 4096 of 76K: 553 / 475 / 450
+constexpr int64_t kUnit8Reduce = 32768, kUnit8Scan = 12288, kUnit16Scan = 49152;
+int reduce_by_mean(int64_t n, int64_t S, bool persistent) {
+  if (n <= kUnit8Reduce * S) return 0;
+  return short_reduce(n, S, persistent) ? 1 : 2;
+}
+int scan_by_mean(int64_t n, int64_t S) {
+  return n <= kUnit8Scan * S ? 0 : n <= kUnit16Scan * S ? 1 : 2;
+}
+
 template <class C>
 hipError_t launch_reduce(const int32_t* in, int64_t n, const int64_t* offsets, int64_t S,
                          int64_t* out, void* ws, hipStream_t s, bool persistent) {
   const SegWs w = carve(ws, n, S, false);
   const int64_t units = S + (n + C::unit - 1) / C::unit;   // at least the units of the call
-  if (persistent && persistent_fits(n, S)) {
+  const bool many_short = short_reduce(n, S, persistent);
+  if (persistent && !many_short) {
     static int resident[64] = {0};
     int64_t g = launch::resident_grid(seg_reduce_persistent_kernel<C>, resident, 1, C::block);
     if (g > units) g = units;
@@ -616,7 +839,11 @@ hipError_t launch_reduce(const int32_t* in, int64_t n, const int64_t* offsets, i
   }
   hipLaunchKernelGGL((plan_kernel<C, false>), dim3(1), dim3(kPlanBlock), 0, s, offsets, n, S,
                      w.total, w.unit_start, out, (uint64_t*)nullptr, (int64_t)0);
-  if (units > 0)
+  if (units > 0 && many_short)
+    hipLaunchKernelGGL(seg_reduce_short_kernel<C>,
+                       dim3((unsigned)((units + C::waves - 1) / C::waves)), dim3(C::block), 0, s,
+                       in, n, offsets, S, w.total, w.unit_start, out);
+  else if (units > 0)
     hipLaunchKernelGGL(seg_reduce_kernel<C>, dim3((unsigned)units), dim3(C::block), 0, s, in, n,
                        offsets, S, w.total, w.unit_start, out);
   return hipGetLastError();
@@ -633,19 +860,27 @@ hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, const int64_t
   const int64_t mu = S + (n + C::unit - 1) / C::unit;
   hipLaunchKernelGGL((plan_kernel<C, true>), dim3(1), dim3(kPlanBlock), 0, s, offsets, n, S,
                      w.total, w.unit_start, (int64_t*)nullptr, w.status, mu);
-  if (mu > 0)
+  if (mu > 0 && short_scan(n, S))
+    hipLaunchKernelGGL(seg_scan_short_kernel<C>,
+                       dim3((unsigned)((mu + C::waves - 1) / C::waves)), dim3(C::block), 0, s, in,
+                       out, n, offsets, S, w.total, w.unit_start, w.status, (WsHeader*)ws);
+  else if (mu > 0)
     hipLaunchKernelGGL(seg_scan_kernel<C>, dim3((unsigned)mu), dim3(C::block), 0, s, in, out, n,
                        offsets, S, w.total, w.unit_start, w.status, (WsHeader*)ws);
   return hipGetLastError();
 }
 
 // The reduce has no 64K unit: holding 16 rounds in 1024 threads spills.
-constexpr const char* kNames[] = {"unit8k", "unit16k", "unit32k", "unit32k_w16", "unit64k_w16"};
-constexpr int kReduceDefaults[tune::kClasses] = {0, 0, 0, 1};
-constexpr int kScanDefaults[tune::kClasses] = {0, 0, 0, 2};
+constexpr const char* kReduceNames[] = {"unit8k", "unit16k", "unit32k", "unit32k_w16", "by_mean"};
+constexpr const char* kScanNames[] = {"unit8k",      "unit16k",     "unit32k",
+                                      "unit32k_w16", "unit64k_w16", "by_mean"};
+constexpr int kReduceByMean = 4, kScanByMean = 5;
+constexpr int kReduceDefaults[tune::kClasses] = {kReduceByMean, kReduceByMean, kReduceByMean,
+                                                 kReduceByMean};
+constexpr int kScanDefaults[tune::kClasses] = {kScanByMean, kScanByMean, kScanByMean, kScanByMean};
 const bool kRegistered =
-    (tune::register_op(tune::kSegReduceI32, "seg_reduce_i32", 4, kNames, kReduceDefaults),
-     tune::register_op(tune::kSegScanI32, "seg_scan_i32", 5, kNames, kScanDefaults), true);
+    (tune::register_op(tune::kSegReduceI32, "seg_reduce_i32", 5, kReduceNames, kReduceDefaults),
+     tune::register_op(tune::kSegScanI32, "seg_scan_i32", 6, kScanNames, kScanDefaults), true);
 
 }  // namespace
 
@@ -660,7 +895,10 @@ int64_t segmented_max_grid(int64_t n, int64_t S) { return max_units(n, S); }
 hipError_t reduce_segmented_i32(const int32_t* in, int64_t n, const int64_t* offsets, int64_t S,
                                 int64_t* out, void* ws, hipStream_t s, bool persistent) {
   (void)kRegistered;
-  switch (tune::get(tune::kSegReduceI32, tune::size_class(tune::kSegReduceI32, n))) {
+  int c = tune::get(tune::kSegReduceI32, tune::size_class(tune::kSegReduceI32, n));
+  persistent = persistent && persistent_fits(n, S);
+  if (c == kReduceByMean) c = reduce_by_mean(n, S, persistent);
+  switch (c) {
     case 1: return launch_reduce<UnitCfg<256, 16>>(in, n, offsets, S, out, ws, s, persistent);
     case 2: return launch_reduce<UnitCfg<512, 16>>(in, n, offsets, S, out, ws, s, persistent);
     case 3: return launch_reduce<UnitCfg<1024, 8>>(in, n, offsets, S, out, ws, s, persistent);
@@ -671,7 +909,9 @@ hipError_t reduce_segmented_i32(const int32_t* in, int64_t n, const int64_t* off
 hipError_t scan_segmented_i32(const int32_t* in, int32_t* out, int64_t n, const int64_t* offsets,
                               int64_t S, void* ws, hipStream_t s) {
   (void)kRegistered;
-  switch (tune::get(tune::kSegScanI32, tune::size_class(tune::kSegScanI32, n))) {
+  int c = tune::get(tune::kSegScanI32, tune::size_class(tune::kSegScanI32, n));
+  if (c == kScanByMean) c = scan_by_mean(n, S);
+  switch (c) {
     case 1: return launch_scan<UnitCfg<256, 16>>(in, out, n, offsets, S, ws, s);
     case 2: return launch_scan<UnitCfg<512, 16>>(in, out, n, offsets, S, ws, s);
     case 3: return launch_scan<UnitCfg<1024, 8>>(in, out, n, offsets, S, ws, s);
