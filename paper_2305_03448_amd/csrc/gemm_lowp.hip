@@ -20,9 +20,13 @@
 //
 // Padding: Mp, Np are multiples of 256 and Kp a multiple of 128 elements;
 // the pre-pass writes zeros there, so the GEMM main loop has no guards.
+#include <algorithm>
+#include <cmath>
+
 #include "common.hpp"
 #include "direct_forms.hpp"
 #include "gemm_direct_nt.hpp"
+#include "gemm_dma.hpp"
 #include "gemm_fp8_fused.hpp"
 #include "gemm_nt.hpp"
 #include "launch.hpp"
@@ -491,6 +495,38 @@ hipError_t launch_nt(const NtOperands& p, int64_t Mp, int64_t Np, hipStream_t s)
   return hipGetLastError();
 }
 
+// 256 x 256 tiles staged to LDS directly (gemm_dma.hpp).
+template <class C, bool kNt>
+__global__ __launch_bounds__(C::threads) void gemm_dma_kernel(NtOperands p, int64_t tiles_m,
+                                                              int64_t tiles_n) {
+  // two arrays: the compiler then sees that one stage's loads do not write
+  // what the other's reads read, and waits only at the barrier
+  __shared__ u32x4 even[C::stage_chunks], odd[C::stage_chunks];
+  const idx_t t = gemm_f32::xcd_tile(block_x(), tiles_m, tiles_n);
+  gemm_nt::dma_tile<C, kNt>(p, t / tiles_n, t % tiles_n, even, odd);
+}
+
+// `bytes`: the call's operands, planes and result.  Beyond the 256 MB that the
+// memory-side cache holds, C goes past it (non-temporal stores), which leaves
+// it to the planes: split BF16 4096^3 (335 MB) 340 against 355 us, FP8 8192^3
+// 600 against 613; below, C is better kept: FP8 4096^3 (235 MB) 107 against 104.
+template <class Mode>
+hipError_t launch_dma(const NtOperands& p, int64_t Mp, int64_t Np, int64_t bytes, hipStream_t s) {
+  using C = DmaCfg<Mode>;
+  const int64_t tm = Mp / C::bm, tn = Np / C::bn;
+  if (bytes > (int64_t(256) << 20))
+    hipLaunchKernelGGL((gemm_dma_kernel<C, true>), dim3((unsigned)(tm * tn)), dim3(C::threads), 0, s,
+                       p, tm, tn);
+  else
+    hipLaunchKernelGGL((gemm_dma_kernel<C, false>), dim3((unsigned)(tm * tn)), dim3(C::threads), 0,
+                       s, p, tm, tn);
+  return hipGetLastError();
+}
+// A tile's rows span less than 2^31 bytes of a plane and less than 2^30 of C.
+bool dma_fits(int64_t row_bytes, int64_t ldc) {
+  return row_bytes < (int64_t(1) << 23) && ldc < (int64_t(1) << 20);
+}
+
 // One launch from the FP32 operands (gemm_fp8_fused.hpp).
 __global__ __launch_bounds__(64 * gemm_fp8::kFusedWaves) void gemm_fp8_fused_kernel(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
@@ -583,7 +619,7 @@ constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
 
 // Times of the fused forms by the tiles a CU gets (us, K in the formulas per
 // 1000).  128 x 128, two blocks a CU: 35 K for one tile, 50 K for two, 84 K
-// for three, 104 K for four, and 3 us of ends a tile (1000 x 1500 x 777 36 us
+// for three, 104 K for four, 120 K for five, and 3 us of ends a tile (1000 x 1500 x 777 36 us
 // against 22.5 in 64 x 128 direct tiles; 2048^3 80 against 92).  256 x 256,
 // eight waves: 68 K a round, 88 K when every CU has one, and 11 us of ends
 // (4096^3 366 us against 430 in 128 x 128 tiles, 3001 x 2777 x 2501 201
@@ -592,7 +628,7 @@ double fused128_us(int64_t M, int64_t N, int64_t K) {
   const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
   const double each = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
   const double pairs = (double)(int64_t)(each / 2), odd = each - 2 * pairs;
-  return (pairs * 50.0 + odd * 35.0) * K * 1e-3 + 3.0 * each;
+  return (pairs * 50.0 + odd * (pairs < 2 ? 35.0 : 20.0)) * K * 1e-3 + 3.0 * each;
 }
 double fused256_us(int64_t M, int64_t N, int64_t K) {
   const double tiles = (double)((M + 255) / 256) * (double)((N + 255) / 256);
@@ -600,12 +636,46 @@ double fused256_us(int64_t M, int64_t N, int64_t K) {
   return rounds * ((68.0 + 20.0 * (tiles < 256 ? tiles / 256 : 1.0)) * K * 1e-3 + 11.0);
 }
 
+// The 256 x 256 tiles staged to LDS directly (us, K per 1000), rounds of one
+// tile a CU: full rounds, and a last one of f x 256 tiles, which runs at a
+// higher clock the fewer there are.
+double rounds_us(int64_t M, int64_t N, double full, double part_a, double part_f, double part_k,
+                 double part_kf2, double K) {
+  const double tiles = (double)((M + 255) / 256) * (double)((N + 255) / 256);
+  const double whole = (double)(int64_t)(tiles / 256), f = tiles / 256 - whole;
+  return whole * full + (f > 0 ? part_a + part_f * f + (part_k + part_kf2 * f * f) * K : 0.0);
+}
+// Split BF16, with the pre-pass over the operands: 176 us at 4096 x 4096 x
+// 2048 against 194 fused, 332 at 4096^3 against 366, 132 at 3072 x 3072 x 2048
+// against 162, 2547 at 8192^3 against 2840; 117 at 2048^3 against 73 in 128 x
+// 128 tiles, and 63 at 4096 x 4096 x 512 against 60.
+double split_dma_us(int64_t M, int64_t N, int64_t K) {
+  const double k = K * 1e-3;
+  const double pre = 8.0 + 8.0 * ((double)M * K + (double)K * N) / 5.9e6;
+  return pre + rounds_us(M, N, 17.0 + 64.0 * k, 15.0, 2.0, 42.0, 22.0, k);
+}
+// FP8, without the pre-pass, which its staged forms share: 4096^3 60 us
+// against 75 in 128 x 128 tiles (with eight waves in 256 x 256 register-staged
+// ones 75, too); 8192 x 4096 x 2048 with the pre-pass 101 against 112, 3072 x
+// 3072 x 4096 77 against 86; 2048^3 43 against 33, 8192 x 4096 x 512 64
+// against 58.
+double fp8_dma_us(int64_t M, int64_t N, int64_t K) {
+  const double k = K * 1e-3;
+  return rounds_us(M, N, 15.0 + 11.2 * k, 5.0, 10.0, 7.3, 3.9, k);
+}
+double fp8_staged128_us(int64_t M, int64_t N, int64_t K) {
+  const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
+  const double each = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
+  return 5.0 + 1.8 * each + (4.2 * each - 0.5) * K * 1e-3;
+}
+
 // "_w8": eight waves (2 x 4) share the tile instead of four (2 x 2);
 // "_fused": the operands split while they are staged (no pre-pass);
 // "by_shape": a fused or a direct form, whichever the call's M, N and K make
 // faster; "dBMxBN": that direct form (by_shape where a row of C is shorter
 // than one load, or a stride is beyond the direct forms');
-// "_p": fragment reads one group of matrix ops ahead (NtCfg kPipe).
+// "_p": fragment reads one group of matrix ops ahead (NtCfg kPipe);
+// "_dma": stages loaded to LDS directly (gemm_dma.hpp).
 // "by_shape" (FP8): one of the forms below by the rule of fp8_by_shape;
 // "fused32x32": one launch from the FP32 operands; "d32x32", "d64x64": direct
 // tiles over the planes.
@@ -614,18 +684,20 @@ constexpr const char* kNamesBf16[] = {"m128n128k32", "m256n128k32", "m128n256k32
                                       "m128n128k32_fused", "m256n256k32_w8d1_fused",
                                       "by_shape", "d128x128", "d64x128", "d128x64", "d64x64",
                                       "d48x48", "d32x64", "d32x32", "d16x64", "d16x32", "d32x16",
-                                      "d16x16"};
+                                      "d16x16", "m256n256k32_dma"};
 constexpr int kByShape = 7, kCountBf16 = (int)(sizeof(kNamesBf16) / sizeof(kNamesBf16[0]));
-static_assert(kCountBf16 == kByShape + 1 + kDirectForms, "one name per configuration");
+constexpr int kBf16Dma = kByShape + 1 + kDirectForms;
+static_assert(kCountBf16 == kBf16Dma + 1, "one name per configuration");
 constexpr int kDefaultsBf16[tune::kClasses] = {kByShape, kByShape, kByShape, kByShape};
 constexpr const char* kNamesFp8[] = {"m128n128k128", "m128n128k64", "m256n128k128",
                                      "m128n256k128", "m256n128k64", "m256n256k64_w8d1",
                                      "m256n256k128_w8d1", "m256n256k128_w8d1_p", "m128n128k128_p",
-                                     "by_shape", "fused32x32", "d32x32", "d64x64"};
+                                     "by_shape", "fused32x32", "d32x32", "d64x64",
+                                     "m256n256k128_dma"};
 constexpr int kFp8ByShape = 9, kCountFp8 = (int)(sizeof(kNamesFp8) / sizeof(kNamesFp8[0]));
 constexpr int kDefaultsFp8[tune::kClasses] = {kFp8ByShape, kFp8ByShape, kFp8ByShape, kFp8ByShape};
 constexpr int kDefaults[tune::kClasses] = {0, 0, 0, 0};
-constexpr int kFp8Fused = 10, kFp8D64 = 12;
+constexpr int kFp8Fused = 10, kFp8D64 = 12, kFp8Dma = 13;
 using Fp8D32 = DirectNtCfg<1, 1, 16, 2>;
 using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;
 
@@ -636,15 +708,16 @@ using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;
 // 1024 x 512 32 against 17).  With up to 256 tiles of 32 x 32, then of 64 x 64,
 // the direct tiles share K among 16 or 8 waves (64 x 64 x 4096 22 against 36
 // us, 128 x 2048 x 2048 20.5 against 27, 1024 x 1024 x 4096 34 against 37).
-// Beyond that the LDS-staged tiles, by M N K.
+// Beyond that the LDS-staged tiles: 128 x 128 or the direct-to-LDS 256 x 256
+// by the times above, for small M N K 128 x 128 with shorter stages.
 int fp8_by_shape(int64_t M, int64_t N, int64_t K, int cls) {
   auto tiles = [&](int64_t t) { return (double)((M + t - 1) / t) * (double)((N + t - 1) / t); };
   constexpr int64_t kOnce = gemm_fp8::kFusedWaves * gemm_fp8::kFusedStep;
   if ((tiles(32) <= 256 && K <= kOnce) || (tiles(32) <= 512 && K <= kOnce / 2)) return kFp8Fused;
   if (tiles(32) <= 256) return kFp8Fused + 1;
   if (tiles(64) <= 256) return kFp8D64;
-  constexpr int kStaged[tune::kClasses] = {1, 0, 8, 7};
-  return kStaged[cls];
+  if (cls < 2) return cls == 0 ? 1 : 0;
+  return fp8_dma_us(M, N, K) < fp8_staged128_us(M, N, K) ? kFp8Dma : 8;
 }
 
 const bool kRegistered =
@@ -709,23 +782,29 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
                        int64_t ldc, int64_t M, int64_t N, int64_t K, void* ws, hipStream_t s) {
   (void)kRegistered;
   int cfg = tune::get(tune::kGemmBf16x3, tune::size_class(tune::kGemmBf16x3, M * N * K));
-  if (cfg >= kByShape && K > 0 && lda <= kDirectMaxLd && ldb <= kDirectMaxLd) {
-    const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
-    if (cfg > kByShape && N >= kDirect[cfg - kByShape - 1].cols)
-      return kDirect[cfg - kByShape - 1].launch(g, s);
-    double us = 0;
-    const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
-    if (us <= fused128_us(M, N, K) && us <= fused256_us(M, N, K)) return d.launch(g, s);
+  const LowpLayout L = lowp_layout(1, M, N, K);
+  const bool dma_ok = dma_fits(L.Kp * 2, ldc);
+  if (cfg == kBf16Dma && !dma_ok) cfg = kByShape;
+  if (cfg >= kByShape && cfg < kBf16Dma) {
+    const double fused = std::min(fused128_us(M, N, K), fused256_us(M, N, K));
+    const double dma = dma_ok && K > 0 ? split_dma_us(M, N, K) : INFINITY;
+    if (K > 0 && lda <= kDirectMaxLd && ldb <= kDirectMaxLd) {
+      const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
+      if (cfg > kByShape && N >= kDirect[cfg - kByShape - 1].cols)
+        return kDirect[cfg - kByShape - 1].launch(g, s);
+      double us = 0;
+      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
+      if (us <= fused && us <= dma) return d.launch(g, s);
+    }
+    cfg = dma < fused ? kBf16Dma : fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;
   }
-  if (cfg >= kByShape) cfg = fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;
-  if (cfg >= 5 && K > 0 && lda <= gemm_nt::kSplitMaxLd && ldb <= gemm_nt::kSplitMaxLd) {
+  if (cfg >= 5 && cfg < kBf16Dma && K > 0 && lda <= gemm_nt::kSplitMaxLd && ldb <= gemm_nt::kSplitMaxLd) {
     const gemm_nt::F32Operands f{A, lda, B, ldb, M, N, K};
     if (cfg == 6) return launch_split<NtCfg<256, 256, 64, Bf16x3Mode, 1, 2, 4>>(f, Cm, ldc, s);
     return launch_split<NtCfg<128, 128, 64, Bf16x3Mode>>(f, Cm, ldc, s);
   }
-  // the pre-pass form (also the fused configurations' path for K = 0 and
+  // the pre-pass forms (also the fused configurations' path for K = 0 and
   // strides past the split source's limit)
-  const LowpLayout L = lowp_layout(1, M, N, K);
   uint8_t* w = (uint8_t*)ws;
   uint16_t *ah = (uint16_t*)(w + L.off[0]), *al = (uint16_t*)(w + L.off[1]);
   uint16_t *bh = (uint16_t*)(w + L.off[2]), *bl = (uint16_t*)(w + L.off[3]);
@@ -736,6 +815,8 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
   NtOperands p{{(const uint8_t*)ah, (const uint8_t*)al},
                {(const uint8_t*)bh, (const uint8_t*)bl},
                L.Kp * 2, Cm, ldc, M, N, nullptr, nullptr};
+  if (cfg == kBf16Dma)
+    return launch_dma<Bf16x3Mode>(p, L.Mp, L.Np, 4 * (M * K + K * N + M * N) + (int64_t)L.total, s);
   switch (cfg) {
     case 1: return launch_nt<NtCfg<256, 128, 64, Bf16x3Mode>>(p, L.Mp, L.Np, s);
     case 2: return launch_nt<NtCfg<128, 256, 64, Bf16x3Mode>>(p, L.Mp, L.Np, s);
@@ -768,6 +849,11 @@ hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     go(B, K, N, ldb, (const float*)part, S, L.Np, qb, L.Np, L.Kp, L.Kp, sb, vin, true);
   });
   NtOperands p{{qa, nullptr}, {qb, nullptr}, L.Kp, Cm, ldc, M, N, sa, sb};
+  if (cfg == kFp8Dma) {
+    if (dma_fits(p.row_bytes, ldc))
+      return launch_dma<Fp8Mode>(p, L.Mp, L.Np, 4 * (M * K + K * N + M * N) + (int64_t)L.total, s);
+    cfg = 7;
+  }
   if (cfg >= kFp8Fused) {
     if (cfg == kFp8D64 && gemm_nt::direct_tile_ok<Fp8D64>(L.Kp))
       return launch_direct_nt<Fp8D64>(p, s);
