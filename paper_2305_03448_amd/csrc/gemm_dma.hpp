@@ -11,15 +11,18 @@
 //
 // What bounds it (4096^3): FP8 1.42 us a stage, where the matrix ops alone
 // take 1.10 and 1.32 without the loads, and 15 us of ends, most of it the
-// 67 MB of C, which all blocks write at once; split BF16 306 us, 224 for the
+// 67 MB of C, which all blocks write at once; split BF16 285 us, 224 for the
 // matrix ops alone: the clock falls to 1.6 GHz under them, so what the loads
 // and reads cost is their energy.  The eight-wave register-staged tile takes
 // 75 us (FP8), and 355 us from the FP32 operands in the split mode.  All of a
 // stage's loads at the start of its second step cost 7 to 13 % more, spread
 // one to a matrix op as here least.
 //
-// Padded planes ([rows][row_bytes], zeros past K, as gemm_nt.hpp), with a
-// tile's rows of a plane below 2^31 bytes.
+// One padded plane per operand ([rows][row_bytes], zeros past K), a tile's rows
+// below 2^31 bytes.  In the split mode its rows hold, for every 32 k, the 32 hi
+// values and then the 32 lo values, so that a stage takes whole 128-byte lines
+// of it (half lines of two planes took 160 us against 145 at 4096 x 4096 x 2048,
+// and at 8192^3, with the pre-pass, 2550 against 2300).
 #pragma once
 #include <type_traits>
 
@@ -33,13 +36,14 @@ struct DmaCfg {
   static constexpr int bm = 256, bn = 256, wm = 2, wn = 2, threads = 256;
   static constexpr int wtm = bm / wm, wtn = bn / wn, fm = wtm / 32, fn = wtn / 32;
   static constexpr int steps = 2;
-  static constexpr int bkb = steps * Mode::step_bytes;      // bytes of K per row and stage
+  static constexpr int part = steps * Mode::step_bytes;     // bytes of one value's plane (hi, lo)
+  static constexpr int bkb = Mode::planes * part;           // bytes per row and stage
   static constexpr int chunks = bkb / 16;
   static constexpr int rows_per_256 = 256 / bkb;
-  static constexpr int plane_chunks = (bm + bn) * chunks;
-  static constexpr int stage_chunks = Mode::planes * plane_chunks;   // 16-byte chunks: 64 KB
+  static constexpr int stage_chunks = (bm + bn) * chunks;   // 16-byte chunks: 64 KB
   static constexpr int rows_per_load = threads / chunks;    // rows one load of the block covers
-  static constexpr int loads = bm / rows_per_load;          // per operand and plane
+  static constexpr int loads = bm / rows_per_load;          // per operand
+  static_assert(bkb == 128, "a stage takes whole lines");
   // a load's rows start at a multiple of the swizzle's period, so a lane's
   // offset in a plane is the same for every load
   static_assert(rows_per_load % (rows_per_256 * chunks) == 0 && 32 % (rows_per_256 * chunks) == 0,
@@ -86,11 +90,9 @@ __device__ __forceinline__ void dma_tile(const NtOperands& p, idx_t tm, idx_t tn
   const idx_t m0 = tm * C::bm, n0 = tn * C::bn;
   const idx_t nk = p.row_bytes / C::bkb;
 
-  // LDS of a stage: [plane][A rows then B rows][chunks], swizzled
-  auto plane = [&](u32x4* buf, int pl) {
-    return matrices(buf, P, C::bm + C::bn, CPR)
-        .idx(pl)
-        .template xor_swizzle<C::rows_per_256, CPR>();
+  // LDS of a stage: [A rows then B rows][chunks], swizzled
+  auto rows_of = [&](u32x4* buf) {
+    return matrix(buf, C::bm + C::bn, CPR).template xor_swizzle<C::rows_per_256, CPR>();
   };
 
   // A load's lanes fill consecutive chunks of LDS: lane t of the block the
@@ -101,19 +103,15 @@ __device__ __forceinline__ void dma_tile(const NtOperands& p, idx_t tm, idx_t tn
                             16u * (uint32_t)((t % CPR) ^ ((row / C::rows_per_256) % CPR));
   const uint32_t load_off = (uint32_t)C::rows_per_load * (uint32_t)p.row_bytes;
   const uint32_t tile_bytes = (uint32_t)C::bm * (uint32_t)p.row_bytes;
-  const uint8_t* first[2][P];
-#pragma unroll
-  for (int pl = 0; pl < P; ++pl) {
-    first[0][pl] = &matrix(p.a[pl], 0, p.row_bytes).at(m0, 0);
-    first[1][pl] = &matrix(p.b[pl], 0, p.row_bytes).at(n0, 0);
-  }
-  // Load l of 2 P loads of stage s into buf; past the last stage the range is
-  // empty and zeros are written.
-  constexpr int kLoads = 2 * P * C::loads;
+  const uint8_t* first[2] = {&matrix(p.a[0], 0, p.row_bytes).at(m0, 0),
+                             &matrix(p.b[0], 0, p.row_bytes).at(n0, 0)};
+  // Load l of the 2 C::loads of stage s into buf; past the last stage the range
+  // is empty and zeros are written.
+  constexpr int kLoads = 2 * C::loads;
   auto load = [&](u32x4* buf, idx_t s, int l) {
-    const int pl = l / (2 * C::loads), op = l / C::loads % 2, i = l % C::loads;
-    const auto rs = buffer_rsrc(first[op][pl], s < nk ? tile_bytes : 0);
-    u32x4* to = buf + pl * C::plane_chunks + op * C::bm * CPR + i * C::threads + w * kWave;
+    const int op = l / C::loads, i = l % C::loads;
+    const auto rs = buffer_rsrc(first[op], s < nk ? tile_bytes : 0);
+    u32x4* to = buf + op * C::bm * CPR + i * C::threads + w * kWave;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         rs, (__attribute__((address_space(3))) void*)to, 16, (int)lane_off,
         (int)((uint32_t)s * C::bkb + (uint32_t)i * load_off), 0, 0);
@@ -128,13 +126,13 @@ __device__ __forceinline__ void dma_tile(const NtOperands& p, idx_t tm, idx_t tn
     const bool is_b = k < C::fn;
     const int frag = is_b ? k : k - C::fn;
     const int row = is_b ? C::bm + wn * C::wtn + col32 : wm * C::wtm + col32;
-    const int ch = (st * Mode::step_bytes + half * LB) / 16;
-    const u32x4 v = (&plane(buf, pl).at(row, ch))[frag * kFragStride];
+    const int ch = (pl * C::part + st * Mode::step_bytes + half * LB) / 16;
+    const u32x4 v = (&rows_of(buf).at(row, ch))[frag * kFragStride];
     auto& to = is_b ? f.b[pl][frag] : f.a[pl][frag];
     if constexpr (LB == 16) {
       to = __builtin_bit_cast(mfma::bf16x8, v);
     } else {
-      const u32x4 u = (&plane(buf, pl).at(row, ch + 1))[frag * kFragStride];
+      const u32x4 u = (&rows_of(buf).at(row, ch + 1))[frag * kFragStride];
       const auto both = __builtin_shufflevector(v, u, 0, 1, 2, 3, 4, 5, 6, 7);
       to = __builtin_bit_cast(mfma::i32x8, both);
     }

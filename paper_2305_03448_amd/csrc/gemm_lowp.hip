@@ -7,7 +7,9 @@
 // in FP32), likewise for b; C ~ Ah*Bh + Ah*Bl + Al*Bh (the Al*Bl term is
 // below FP32 resolution).  Pre-pass: A -> Ah, Al as [Mp][Kp] bf16 (an
 // element-wise pass), B -> Bh^T, Bl^T as [Np][Kp] bf16 (an LDS-tiled
-// transpose, split on the way).
+// transpose, split on the way); for the direct-to-LDS tiles one launch and one
+// plane per operand (split_paired_kernel); the fused and the direct forms take
+// the FP32 operands.
 //
 // FP8.  alpha_i = max_k |a_ik|; q_ik = e4m3(a_ik * (448 / alpha_i)) with one
 // FP32 division and one FP32 multiply; s_i = alpha_i / 448 (an all-zero row
@@ -386,6 +388,93 @@ __device__ __forceinline__ auto encode_col(const f32x4 (&v)[kR], int c, float in
   return e;
 }
 
+// The split-BF16 pre-pass of the direct-to-LDS tiles, one launch: blocks of 512
+// k x 32 columns of B as above, then blocks of 2048 groups of 4 consecutive k
+// of A.  Both write rows that hold, for every 32 k, 32 hi and then 32 lo
+// values: whole lines.  Bound by memory: 43 us at 4096 x 4096 x 4096 (268
+// MB) where the two launches above take 22 and 28.
+constexpr int kPairGroups = 8;   // groups of A per thread
+
+// 8 values, hi and lo, at group g (of 8 k) of a paired row.
+__device__ __forceinline__ void store_pair(u32x4* row, idx_t g, const float (&v)[8]) {
+  const lowp::Split4 x = lowp::split_bf16x4(v[0], v[1], v[2], v[3]);
+  const lowp::Split4 y = lowp::split_bf16x4(v[4], v[5], v[6], v[7]);
+  const auto join = [](lowp::bf16x4_bits p, lowp::bf16x4_bits q) {
+    const lowp::u32x2_bits a = __builtin_bit_cast(lowp::u32x2_bits, p);
+    const lowp::u32x2_bits b = __builtin_bit_cast(lowp::u32x2_bits, q);
+    return u32x4{a[0], a[1], b[0], b[1]};
+  };
+  row[g / 4 * 8 + g % 4] = join(x.hi, y.hi);
+  row[g / 4 * 8 + 4 + g % 4] = join(x.lo, y.lo);
+}
+
+__global__ __launch_bounds__(kBlock) void split_paired_kernel(
+    const float* __restrict__ A, int64_t M, int64_t lda, u32x4* __restrict__ pa, int64_t rows_out,
+    const float* __restrict__ B, int64_t N, int64_t ldb, u32x4* __restrict__ pb, int64_t n_out,
+    int64_t K, int64_t k_out, int64_t k_blocks, int64_t b_blocks) {
+  const idx_t blk = block_x().index();
+  const int t = (int)thread_x<kBlock>().index();
+  const idx_t row_groups = k_out / 8;            // groups of a row; twice as many 16-byte groups
+  if (blk < b_blocks) {
+    constexpr int kR = kEncodeRows;
+    const int w = t / kWave, lane = t % kWave;
+    const idx_t n = blk / k_blocks * 32 + 4 * (lane % 8);
+    const idx_t k = ((blk % k_blocks * 4 + w) * 8 + lane / 8) * kR;
+    if (k >= k_out) return;
+    f32x4 v[kR];
+    load_cols<kR, false>(B, K, N, ldb, k, n, blk / k_blocks * 32 + 32 <= N, v);
+    auto out = matrix(pb, n_out, 2 * row_groups);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int h = 0; h < kR / 8; ++h) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = v[8 * h + j][c];
+        store_pair(&out.at(n + c, 0), k / 8 + h, x);
+      }
+    return;
+  }
+  auto a = matrix(A, M, lda);
+  auto out = matrix((u16x4*)pa, rows_out, 4 * row_groups);
+  const idx_t per_row = k_out / 4, total = rows_out * per_row;
+  const idx_t g0 = (blk - b_blocks) * (kBlock * kPairGroups) + t;
+  f32x4 x[kPairGroups];
+  idx_t row[kPairGroups], at[kPairGroups];
+#pragma unroll
+  for (int i = 0; i < kPairGroups; ++i) {
+    const idx_t g = g0 + kBlock * i;
+    row[i] = g / per_row;
+    at[i] = g % per_row;
+    const idx_t c = 4 * at[i];
+    if (row[i] < M && c + 4 <= K) {
+      x[i] = *(const f32x4_any*)&a.at(row[i], c);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[i][j] = row[i] < M && c + j < K ? a.at(row[i], c + j) : 0.f;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kPairGroups; ++i) {
+    if (g0 + kBlock * i >= total) continue;
+    const lowp::Split4 sp = lowp::split_bf16x4(x[i][0], x[i][1], x[i][2], x[i][3]);
+    const idx_t to = at[i] / 8 * 16 + at[i] % 8;       // 8 groups of hi, then 8 of lo
+    out.at(row[i], to) = sp.hi;
+    out.at(row[i], to + 8) = sp.lo;
+  }
+}
+
+hipError_t launch_split_paired(const float* A, int64_t M, int64_t lda, void* pa, int64_t Mp,
+                               const float* B, int64_t N, int64_t ldb, void* pb, int64_t Np,
+                               int64_t K, int64_t Kp, hipStream_t s) {
+  const int64_t k_blocks = (Kp + 511) / 512, b_blocks = k_blocks * (Np / 32);
+  const int64_t a_blocks = (Mp * (Kp / 4) + kBlock * kPairGroups - 1) / (kBlock * kPairGroups);
+  hipLaunchKernelGGL(split_paired_kernel, dim3((unsigned)(b_blocks + a_blocks)), dim3(kBlock),
+                     0, s, A, M, lda, (u32x4*)pa, Mp, B, N, ldb, (u32x4*)pb, Np, K, Kp, k_blocks,
+                     b_blocks);
+  return hipGetLastError();
+}
+
 template <int kW, bool kNt>
 __global__ __launch_bounds__(kBlock) void quant_cols_t_kernel(const float* __restrict__ B,
                                                               int64_t K, int64_t N, int64_t ldb,
@@ -642,8 +731,8 @@ __global__ __launch_bounds__(C::threads) void gemm_dma_kernel(NtOperands p, int6
 
 // `bytes`: the call's operands, planes and result.  Beyond the 256 MB that the
 // memory-side cache holds, C goes past it (non-temporal stores), which leaves
-// it to the planes: split BF16 4096^3 (335 MB) 340 against 355 us, FP8 8192^3
-// 600 against 613; below, C is better kept: FP8 4096^3 (235 MB) 107 against 104.
+// it to the planes: split BF16 4096^3 (335 MB) 2 to 5 % faster, FP8 8192^3 2 %;
+// below, C is better kept: FP8 4096^3 (235 MB) 107 us against 104.
 template <class Mode>
 hipError_t launch_dma(const NtOperands& p, int64_t Mp, int64_t Np, int64_t bytes, hipStream_t s) {
   using C = DmaCfg<Mode>;
@@ -753,7 +842,7 @@ constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
 
 // Times of the fused forms by the tiles a CU gets (us, K in the formulas per
 // 1000).  128 x 128, two blocks a CU: 35 K for one tile, 50 K for two, 84 K
-// for three, 104 K for four, 120 K for five, and 3 us of ends a tile (1000 x 1500 x 777 36 us
+// for three, 104 K for four, 117 K for five, and 3 us of ends a tile (1000 x 1500 x 777 36 us
 // against 22.5 in 64 x 128 direct tiles; 2048^3 80 against 92).  256 x 256,
 // eight waves: 68 K a round, 88 K when every CU has one, and 11 us of ends
 // (4096^3 366 us against 430 in 128 x 128 tiles, 3001 x 2777 x 2501 201
@@ -762,7 +851,7 @@ double fused128_us(int64_t M, int64_t N, int64_t K) {
   const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
   const double each = tiles <= 256 ? 1.0 : (double)(int64_t)((tiles + 255) / 256);
   const double pairs = (double)(int64_t)(each / 2), odd = each - 2 * pairs;
-  return (pairs * 50.0 + odd * (pairs < 2 ? 35.0 : 20.0)) * K * 1e-3 + 3.0 * each;
+  return (pairs * 50.0 + odd * (pairs < 2 ? 35.0 : 17.0)) * K * 1e-3 + 3.0 * each;
 }
 double fused256_us(int64_t M, int64_t N, int64_t K) {
   const double tiles = (double)((M + 255) / 256) * (double)((N + 255) / 256);
@@ -779,14 +868,14 @@ double rounds_us(int64_t M, int64_t N, double full, double part_a, double part_f
   const double whole = (double)(int64_t)(tiles / 256), f = tiles / 256 - whole;
   return whole * full + (f > 0 ? part_a + part_f * f + (part_k + part_kf2 * f * f) * K : 0.0);
 }
-// Split BF16, with the pre-pass over the operands: 176 us at 4096 x 4096 x
-// 2048 against 194 fused, 332 at 4096^3 against 366, 132 at 3072 x 3072 x 2048
-// against 162, 2547 at 8192^3 against 2840; 117 at 2048^3 against 73 in 128 x
-// 128 tiles, and 63 at 4096 x 4096 x 512 against 60.
+// Split BF16, with the pre-pass over the operands: 169 us at 4096 x 4096 x
+// 2048 against 194 fused, 329 at 4096^3 against 366, 126 at 3072 x 3072 x 2048
+// against 162, 2300 at 8192^3 against 2840; 111 at 2048^3 against 73 in 128 x
+// 128 tiles, and 58 at 4096 x 4096 x 512 against 57.
 double split_dma_us(int64_t M, int64_t N, int64_t K) {
   const double k = K * 1e-3;
-  const double pre = 8.0 + 8.0 * ((double)M * K + (double)K * N) / 5.9e6;
-  return pre + rounds_us(M, N, 17.0 + 64.0 * k, 15.0, 2.0, 42.0, 22.0, k);
+  const double pre = 7.0 + 8.0 * ((double)M * K + (double)K * N) / 7.2e6;
+  return pre + rounds_us(M, N, 14.0 + 64.0 * k, 11.0, 3.0, 40.0, 22.0, k);
 }
 // FP8, without the pre-pass, which its staged forms share: 4096^3 60 us
 // against 75 in 128 x 128 tiles (with eight waves in 256 x 256 register-staged
@@ -914,7 +1003,7 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
   (void)kRegistered;
   int cfg = tune::get(tune::kGemmBf16x3, tune::size_class(tune::kGemmBf16x3, M * N * K));
   const LowpLayout L = lowp_layout(1, M, N, K);
-  const bool dma_ok = dma_fits(L.Kp * 2, ldc);
+  const bool dma_ok = dma_fits(L.Kp * 4, ldc);
   if (cfg == kBf16Dma && !dma_ok) cfg = kByShape;
   if (cfg >= kByShape && cfg < kBf16Dma) {
     const double fused = std::min(fused128_us(M, N, K), fused256_us(M, N, K));
@@ -939,6 +1028,16 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
   uint8_t* w = (uint8_t*)ws;
   uint16_t *ah = (uint16_t*)(w + L.off[0]), *al = (uint16_t*)(w + L.off[1]);
   uint16_t *bh = (uint16_t*)(w + L.off[2]), *bl = (uint16_t*)(w + L.off[3]);
+  if (cfg == kBf16Dma) {
+    const int64_t bytes = 4 * (M * K + K * N + M * N) + (int64_t)L.total;
+    const hipError_t e =
+        launch_split_paired(A, M, lda, ah, L.Mp, B, N, ldb, bh, L.Np, K, L.Kp, s);
+    if (e != hipSuccess) return e;
+    return launch_dma<Bf16x3Mode>(NtOperands{{(const uint8_t*)ah, nullptr},
+                                             {(const uint8_t*)bh, nullptr},
+                                             L.Kp * 4, Cm, ldc, M, N, nullptr, nullptr},
+                                  L.Mp, L.Np, bytes, s);
+  }
   hipLaunchKernelGGL(split_rows_kernel, dim3(grid_for(L.Mp * (L.Kp / 4))), dim3(kBlock), 0, s, A,
                      M, K, lda, ah, al, L.Mp, L.Kp, L.Kp, f4_ok(A, lda), true);
   hipLaunchKernelGGL(split_cols_t_kernel, dim3((unsigned)(L.Kp / 64), (unsigned)(L.Np / 64)),
@@ -946,8 +1045,6 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
   NtOperands p{{(const uint8_t*)ah, (const uint8_t*)al},
                {(const uint8_t*)bh, (const uint8_t*)bl},
                L.Kp * 2, Cm, ldc, M, N, nullptr, nullptr};
-  if (cfg == kBf16Dma)
-    return launch_dma<Bf16x3Mode>(p, L.Mp, L.Np, 4 * (M * K + K * N + M * N) + (int64_t)L.total, s);
   switch (cfg) {
     case 1: return launch_nt<NtCfg<256, 128, 64, Bf16x3Mode>>(p, L.Mp, L.Np, s);
     case 2: return launch_nt<NtCfg<128, 256, 64, Bf16x3Mode>>(p, L.Mp, L.Np, s);
