@@ -180,8 +180,8 @@ DESC_HD bool lookback_in_segment(idx_t j, idx_t window, int lane) { return 64 * 
 // l0 + per, ... and step l takes tile t(l); the walk ends at the first
 // t(l) >= T, t growing with l.  When B is a multiple of the 8 XCDs (blocks
 // are dispatched round-robin over them, block b running on XCD b mod 8), the
-// tile sequence is cut into runs of 64 consecutive tiles, run r going to XCD
-// r mod 8: l0 = b / 8, per = B / 8, t(l) = (8 (l / 64) + b mod 8) 64 + l mod 64.
+// tile sequence is cut into runs of R = kRun consecutive tiles, run r going to
+// XCD r mod 8: l0 = b / 8, per = B / 8, t(l) = (8 (l / R) + b mod 8) R + l mod R.
 // Otherwise l0 = b, per = B, t(l) = l.
 struct TileWalk {
   idx_t first, per, xcd;
