@@ -331,15 +331,108 @@ __global__ __launch_bounds__(kBlock) void fp8_prepass_kernel(
     quant_row<kNt>(A, M, K, lda, qa, rows_out, k_out, ldqa, sa, a_vec_in, true, blk - col_blocks);
 }
 
-// Encode B with its column scales and write it transposed: qt is n_out x k_out
-// (stride ldq).  A thread holds 16 consecutive k of four columns, so it stores
+// Encode tiles of 64 k x 64 columns of B with their column scales and
+// write them transposed: qt is n_out x k_out (stride ldq).  A block
+// takes one k tile of one column block; the first block of each column
+// block also writes the column scales.  The tile's loads are issued before
+// the column maxima are gathered from the slice partials, so the two sets
+// of loads are in flight together.  Reads run along n (thread = 4 columns
+// of one row), writes along k (thread = 4 consecutive k, one 4-byte store).
+__global__ __launch_bounds__(kBlock) void quant_cols_tile_kernel(const float* __restrict__ B,
+                                                                 int64_t K, int64_t N, int64_t ldb,
+                                                                 const float* __restrict__ part,
+                                                                 int64_t nslices, int64_t ldp,
+                                                                 uint8_t* __restrict__ qt,
+                                                                 int64_t n_out, int64_t k_out,
+                                                                 int64_t ldq,
+                                                                 float* __restrict__ scale,
+                                                                 bool vec_in, bool vec_out) {
+  constexpr int kKT = 64;
+  constexpr int kRows = kKT / 16;               // rows of the tile per thread
+  constexpr int kLanesPerRow = kKT / 4;         // threads per output row
+  constexpr int kOutRows = kBlock / kLanesPerRow;
+  __shared__ uint8_t codes[kKT * 68];
+  __shared__ float inv_s[64];
+  __shared__ float pmax[4][64];
+  auto kt = block_x();
+  auto nt = block_y();
+  auto thread = thread_x<kBlock>();
+  auto tile = matrix(codes, kKT, 68);
+  auto b = matrix(B, K, ldb);
+  auto pm = matrix(part, nslices, ldp);
+  auto out = matrix(qt, n_out, ldq);
+  const idx_t n0 = nt.index() * 64, k0 = kt.index() * kKT;
+  const int tx = (int)thread.index() % 16, ty = (int)thread.index() / 16;
+  f32x4 v[kRows];
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {             // rows ty + 16 i, columns 4 tx ..
+    const idx_t r = ty + 16 * i, c = 4 * tx;
+    if (vec_in && k0 + r < K && n0 + c + 4 <= N) {
+      v[i] = *(const f32x4*)&b.at(k0 + r, n0 + c);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        v[i][j] = (k0 + r < K && n0 + c + j < N) ? b.at(k0 + r, n0 + c + j) : 0.f;
+    }
+  }
+  {
+    // column maxima of the 64 columns from the slice partials: thread
+    // (g, c) takes slices g, g + 4, ... of column c (loads coalesced along
+    // the columns, independent, so they are in flight together)
+    const int c = (int)thread.index() % 64, g = (int)thread.index() / 64;
+    const idx_t n = n0 + c;
+    float m = 0.f;
+    if (n < N)
+#pragma unroll 8
+      for (idx_t sl = g; sl < nslices; sl += 4) m = fmaxf(m, pm.at(sl, n));
+    pmax[g][c] = m;
+  }
+  sync(thread);
+  if (thread.index() < 64) {
+    const int c = (int)thread.index();
+    const idx_t n = n0 + c;
+    const float m = fmaxf(fmaxf(pmax[0][c], pmax[1][c]), fmaxf(pmax[2][c], pmax[3][c]));
+    inv_s[c] = m > 0.f ? 448.0f / m : 1.0f;
+    if (kt.index() == 0 && n < n_out) array(scale, n_out)[n] = m / 448.0f;
+  }
+  sync(thread);
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    const idx_t r = ty + 16 * i, c = 4 * tx;
+    uint32_t keep = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) keep |= (k0 + r < K && n0 + c + j < N) ? (0xffu << (8 * j)) : 0u;
+    const uint32_t w = lowp::e4m3x4(v[i][0] * inv_s[c], v[i][1] * inv_s[c + 1],
+                                    v[i][2] * inv_s[c + 2], v[i][3] * inv_s[c + 3]) & keep;
+    *(u8x4*)&tile.at(r, c) = __builtin_bit_cast(u8x4, w);
+  }
+  sync(thread);
+  const int ox = (int)thread.index() % kLanesPerRow, oy = (int)thread.index() / kLanesPerRow;
+#pragma unroll
+  for (int i = 0; i < 64 / kOutRows; ++i) {     // output rows oy + kOutRows i, k = 4 ox ..
+    const idx_t c = oy + kOutRows * i, r = 4 * ox;
+    if (n0 + c >= n_out) continue;
+    u8x4 e;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = tile.at(r + j, c);
+    if (vec_out && k0 + r + 4 <= k_out) {
+      *(u8x4*)&out.at(n0 + c, k0 + r) = e;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (k0 + r + j < k_out) out.at(n0 + c, k0 + r + j) = e[j];
+    }
+  }
+}
+
+// The same encode of large matrices and of unaligned ones.  A thread holds 16 consecutive k of four columns, so it stores
 // 16 codes of a column at once and nothing passes through LDS; a wave is 128 k
 // x 32 columns, whole 128-byte lines on both sides; kW of a block's four waves
 // lie along k, the others along the columns.  The values are loaded before the
 // column maxima are gathered from the slice partials, so the two sets of loads
 // are in flight together; the first block of each column block also writes the
-// column scales.  Bound by memory: 8192 x 8192 60 us where 4-byte stores of
-// tiles transposed through LDS took 70; 4096 x 4096 18.3 both.
+// column scales.  Bound by memory: 8192 x 8192 60 us where tiles of 128 k
+// through LDS took 70.
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // any element alignment
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 constexpr int kEncodeRows = 16;   // k per thread
@@ -525,16 +618,29 @@ __global__ __launch_bounds__(kBlock) void quant_cols_t_kernel(const float* __res
   }
 }
 
-template <bool kNt, class... Args>
-hipError_t launch_cols_t(int64_t k_out, int64_t n_out, hipStream_t s, Args... args) {
-  if (k_out >= 512)
+// Which encode: the LDS tiles up to 8192 of them, since they make four times
+// the blocks (3072 x 512 6.1 us against 7.9, 2560 x 3072 12.3 / 15.7, 4096 x
+// 4096 18.5 both), but not where their loads would be single ones (B not
+// aligned to 16 bytes).
+template <bool kNt>
+hipError_t launch_cols_t(const float* B, int64_t K, int64_t N, int64_t ldb, const float* part,
+                         int64_t nslices, int64_t ldp, uint8_t* qt, int64_t n_out, int64_t k_out,
+                         int64_t ldq, float* scale, bool vec_in, bool vec_out, hipStream_t s) {
+  const int64_t tk = (k_out + 63) / 64, tn = (n_out + 63) / 64;
+  if (tk * tn <= 8192 && vec_in)
+    hipLaunchKernelGGL(quant_cols_tile_kernel, dim3((unsigned)tk, (unsigned)tn), dim3(kBlock), 0, s,
+                       B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, vec_in,
+                       vec_out);
+  else if (k_out >= 512)
     hipLaunchKernelGGL((quant_cols_t_kernel<4, kNt>),
                        dim3((unsigned)((k_out + 511) / 512), (unsigned)((n_out + 31) / 32)),
-                       dim3(kBlock), 0, s, args...);
+                       dim3(kBlock), 0, s, B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq,
+                       scale);
   else
     hipLaunchKernelGGL((quant_cols_t_kernel<1, kNt>),
                        dim3((unsigned)((k_out + 127) / 128), (unsigned)((n_out + 127) / 128)),
-                       dim3(kBlock), 0, s, args...);
+                       dim3(kBlock), 0, s, B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq,
+                       scale);
   return hipGetLastError();
 }
 
@@ -994,8 +1100,8 @@ hipError_t quant_e4m3_cols(const float* B, int64_t K, int64_t N, int64_t ldb, ui
   hipLaunchKernelGGL(colmax_partial_kernel,
                      dim3((unsigned)((N + 4 * kBlock - 1) / (4 * kBlock)), (unsigned)S),
                      dim3(kBlock), 0, s, B, K, N, ldb, rows_per, part, N, f4_ok(B, ldb));
-  return launch_cols_t<false>(K, N, s, B, K, N, ldb, (const float*)part, S, N, qt, N, K, ldq,
-                              scale);
+  return launch_cols_t<false>(B, K, N, ldb, part, S, N, qt, N, K, ldq, scale, f4_ok(B, ldb),
+                              w_ok(qt, ldq, 1), s);
 }
 
 hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb, float* Cm,
@@ -1087,8 +1193,8 @@ hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, fl
       hipLaunchKernelGGL(fp8_prepass_kernel<nt()>, dim3((unsigned)(cblocks * S + L.Mp)),
                          dim3(kBlock), 0, s, A, M, K, lda, qa, L.Mp, L.Kp, L.Kp, sa, f4_ok(A, lda),
                          B, N, ldb, rows_per, part, L.Np, f4_ok(B, ldb), cblocks, S);
-      return launch_cols_t<nt()>(L.Kp, L.Np, s, B, K, N, ldb, (const float*)part, S, L.Np, qb,
-                                 L.Np, L.Kp, L.Kp, sb);
+      return launch_cols_t<nt()>(B, K, N, ldb, part, S, L.Np, qb, L.Np, L.Kp, L.Kp, sb,
+                                 f4_ok(B, ldb), true, s);
     };
     (void)(bytes > (int64_t(256) << 20) ? two(std::true_type{}) : two(std::false_type{}));
   }
