@@ -64,16 +64,31 @@ inline double rounds_us(int64_t M, int64_t N, int64_t K, int bm, int bn, double 
   return rounds * ((double)K * ns_per_k * 1e-3 + ends);
 }
 
+// What a round of larger FP32 tiles takes beyond that when there are several:
+// measured on 1661 x 2742 to 3001 x 3001 at K = 51, 200 and 801 (64 x 128 at
+// K = 200: 14.7 us a round where 9.8 were estimated, and 44 us in three rounds
+// against 34 in the LDS-staged tile).
+inline double later_rounds_us(int bm, int bn, int64_t K) {
+  const int area = bm * bn;
+  if (area < 6144) return 0.0;
+  if (area == 9216) return K < 100 ? 0.4 : K < 512 ? 1.5 : 0.0;
+  if (area < 8192) return K < 100 ? 0.7 : K < 512 ? 2.5 : 1.0;
+  return K < 100 ? 2.0 : K < 512 ? 5.0 : 1.0;
+}
+
 // The fastest of `count` direct forms by that estimate (the last one, 16 x 16,
 // takes any N).
 inline const DirectForm& best_direct(const DirectForm* forms, int count, int64_t M, int64_t N,
-                                     int64_t K, double* us) {
+                                     int64_t K, bool fp32, double* us) {
   const DirectForm* best = &forms[count - 1];
   *us = 1e300;
   for (int i = 0; i < count; ++i) {
     const DirectForm& f = forms[i];
     if (N < f.cols) continue;
-    const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, 1.5 + f.bm * f.bn / 8192.0);
+    double ends = 1.5 + f.bm * f.bn / 8192.0;
+    if (fp32 && ((M + f.bm - 1) / f.bm) * ((N + f.bn - 1) / f.bn) > 256)
+      ends += later_rounds_us(f.bm, f.bn, K);
+    const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, ends);
     if (t < *us) { best = &f; *us = t; }
   }
   return *best;

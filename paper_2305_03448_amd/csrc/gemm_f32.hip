@@ -171,16 +171,16 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
       return kDirect[cfg - kByShape - 1].launch(g, s);
     // The LDS-staged 128 x 128 tile, up to three blocks a CU, is the faster
     // one per unit of K once several rounds of its tiles run: 67 ns a round
-    // of 256 tiles for one round, 63 for two, 58-60 from four on, and 3 us of
-    // ends (4096^3: 941 us against 1044 in direct tiles; 8192 x 8192 x 64: 94
+    // of 256 tiles for one round, 63 for two, 58-60 from four on, and 2 us of
+    // ends, 4 at short K (4096^3: 941 us against 1044 in direct tiles; 8192 x 8192 x 64: 94
     // against 115; but 1536 x 3072 x 2048, whose 288 tiles leave a second
     // round nearly empty: 260 against 171 us in 96 x 64 direct tiles).
     if (strides) {
       double us = 0;
-      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
+      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, true, &us);
       const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
       const double ns = 58.0 + 9.0 / (tiles <= 256 ? 1.0 : tiles / 256);
-      if (!gemm_f32::clamped_tile<Staged>(g) || us <= rounds_us(M, N, K, 128, 128, ns, 3.0))
+      if (!gemm_f32::clamped_tile<Staged>(g) || us <= rounds_us(M, N, K, 128, 128, ns, K < 512 ? 4.0 : 2.0))
         return d.launch(g, s);
     }
     // whole tiles of aligned rows keep the form without clamps (4096^3: 941

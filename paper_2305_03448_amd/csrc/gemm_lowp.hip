@@ -620,14 +620,14 @@ __global__ __launch_bounds__(kBlock) void quant_cols_t_kernel(const float* __res
 
 // Which encode: the LDS tiles up to 8192 of them, since they make four times
 // the blocks (3072 x 512 6.1 us against 7.9, 2560 x 3072 12.3 / 15.7, 4096 x
-// 4096 18.5 both), but not where their loads would be single ones (B not
-// aligned to 16 bytes).
+// 4096 18.5 both); up to 2048 where their loads are single ones (B not aligned
+// to 16 bytes: 2110 x 1593 2 us ahead of the other's 280 blocks).
 template <bool kNt>
 hipError_t launch_cols_t(const float* B, int64_t K, int64_t N, int64_t ldb, const float* part,
                          int64_t nslices, int64_t ldp, uint8_t* qt, int64_t n_out, int64_t k_out,
                          int64_t ldq, float* scale, bool vec_in, bool vec_out, hipStream_t s) {
   const int64_t tk = (k_out + 63) / 64, tn = (n_out + 63) / 64;
-  if (tk * tn <= 8192 && vec_in)
+  if (tk * tn <= 2048 || (tk * tn <= 8192 && vec_in))
     hipLaunchKernelGGL(quant_cols_tile_kernel, dim3((unsigned)tk, (unsigned)tn), dim3(kBlock), 0, s,
                        B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, vec_in,
                        vec_out);
@@ -965,14 +965,16 @@ double fused256_us(int64_t M, int64_t N, int64_t K) {
   return rounds * ((68.0 + 20.0 * (tiles < 256 ? tiles / 256 : 1.0)) * K * 1e-3 + 11.0);
 }
 
-// The 256 x 256 tiles staged to LDS directly (us, K per 1000), rounds of one
+// The 256 x 256 tiles staged to LDS directly (us, K per 1000), in rounds of one
 // tile a CU: full rounds, and a last one of f x 256 tiles, which runs at a
 // higher clock the fewer there are.
-double rounds_us(int64_t M, int64_t N, double full, double part_a, double part_f, double part_k,
-                 double part_kf2, double K) {
+struct Rounds {
+  double whole, f;
+};
+Rounds rounds256(int64_t M, int64_t N) {
   const double tiles = (double)((M + 255) / 256) * (double)((N + 255) / 256);
-  const double whole = (double)(int64_t)(tiles / 256), f = tiles / 256 - whole;
-  return whole * full + (f > 0 ? part_a + part_f * f + (part_k + part_kf2 * f * f) * K : 0.0);
+  const double whole = (double)(int64_t)(tiles / 256);
+  return {whole, tiles / 256 - whole};
 }
 // Split BF16, with the pre-pass over the operands: 169 us at 4096 x 4096 x
 // 2048 against 194 fused, 329 at 4096^3 against 366, 126 at 3072 x 3072 x 2048
@@ -981,7 +983,10 @@ double rounds_us(int64_t M, int64_t N, double full, double part_a, double part_f
 double split_dma_us(int64_t M, int64_t N, int64_t K) {
   const double k = K * 1e-3;
   const double pre = 7.0 + 8.0 * ((double)M * K + (double)K * N) / 7.2e6;
-  return pre + rounds_us(M, N, 14.0 + 64.0 * k, 11.0, 3.0, 40.0, 22.0, k);
+  const Rounds r = rounds256(M, N);
+  const double full = std::max(14.0 + 64.0 * k, 24.0 + 34.0 * k);   // short K: bound by C
+  return pre + r.whole * full +
+         (r.f > 0 ? 11.0 + 3.0 * r.f + (40.0 + 22.0 * r.f * r.f) * k : 0.0);
 }
 // FP8, without the pre-pass, which its staged forms share: 4096^3 60 us
 // against 75 in 128 x 128 tiles (with eight waves in 256 x 256 register-staged
@@ -990,7 +995,8 @@ double split_dma_us(int64_t M, int64_t N, int64_t K) {
 // against 58.
 double fp8_dma_us(int64_t M, int64_t N, int64_t K) {
   const double k = K * 1e-3;
-  return rounds_us(M, N, 15.0 + 11.2 * k, 5.0, 10.0, 7.3, 3.9, k);
+  const Rounds r = rounds256(M, N);
+  return r.whole * (15.0 + 11.2 * k) + (r.f > 0 ? 7.0 + 10.0 * r.f + (7.3 + 3.9 * r.f) * k : 0.0);
 }
 double fp8_staged128_us(int64_t M, int64_t N, int64_t K) {
   const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
@@ -1119,7 +1125,7 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
       if (cfg > kByShape && N >= kDirect[cfg - kByShape - 1].cols)
         return kDirect[cfg - kByShape - 1].launch(g, s);
       double us = 0;
-      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, &us);
+      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, false, &us);
       if (us <= fused && us <= dma) return d.launch(g, s);
     }
     cfg = dma < fused ? kBf16Dma : fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;
