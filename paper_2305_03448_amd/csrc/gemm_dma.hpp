@@ -11,7 +11,7 @@
 //
 // What bounds it (4096^3): FP8 1.42 us a stage, where the matrix ops alone
 // take 1.10 and 1.32 without the loads, and 15 us of ends, most of it the
-// 67 MB of C, which all blocks write at once; split BF16 285 us, 224 for the
+// 67 MB of C, which all blocks write at once; split BF16 285 to 320 us, 224 for the
 // matrix ops alone: the clock falls to 1.6 GHz under them, so what the loads
 // and reads cost is their energy.  The eight-wave register-staged tile takes
 // 75 us (FP8), and 355 us from the FP32 operands in the split mode.  All of a
