@@ -168,6 +168,20 @@ DESC_HD SegUnit seg_unit(const VO& off, const VU& unit_start, int64_t n, int64_t
   return seg_unit_of(off, unit_start, n, unit, u, seg_of_unit(unit_start, S, u));
 }
 
+// With kW units to a block, the units that block b takes, out of `total`:
+// never one past `bound`, the units of non-decreasing offsets at most, for
+// which the caller sized what a unit writes (offsets that run backwards can
+// plan more; those units are left out).
+struct BlockRange {
+  idx_t first;
+  int count;             // <= 0: none
+};
+template <int kW>
+DESC_HD BlockRange block_units(idx_t b, idx_t total, idx_t bound) {
+  const idx_t first = b * kW, left = (total < bound ? total : bound) - first;
+  return BlockRange{first, left < kW ? (left > 0 ? (int)left : 0) : kW};
+}
+
 // Decoupled look-back over the earlier units of a segment: at window w a
 // whole wave inspects the status words of units u - 1 - 64 w - lane, the
 // lanes with 64 w + lane < j taking part (unit u is unit j of its segment),

@@ -656,31 +656,32 @@ __device__ __forceinline__ bool is_short(const UnitInfo& ui) {
 }
 template <class C>
 __device__ __forceinline__ void find_units(const int64_t* offsets, const int64_t* unit_start,
-                                           int64_t n, int64_t S, int64_t total,
+                                           int64_t n, int64_t S, layout::BlockRange mine,
                                            BlockUnits<C>& bu) {
   auto thread = thread_x<C::block>();
   const int w = (int)wave_of_block<C::block>().index();
-  const idx_t u0 = block_x().index() * C::waves, u = u0 + w;
-  if (u < total) {
+  if (w < mine.count) {
+    const idx_t u = mine.first + w;
     const layout::SegUnit su =
         layout::seg_unit_of(array(offsets, S + 1), array(unit_start, S + 1), n, C::unit, u,
                             wave_owner(unit_start, S, u));
     if (lane_of_wave().index() == 0)
       bu.ui[w] = UnitInfo{su.seg, su.j, su.begin, su.len, su.single};
   }
-  if (thread.index() == 0) bu.count = total - u0 < C::waves ? (int)(total - u0) : C::waves;
+  if (thread.index() == 0) bu.count = mine.count;
   sync(thread);
 }
 
 template <class C>
 __global__ __launch_bounds__(C::block) void seg_reduce_short_kernel(
     const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ offsets, int64_t S,
-    const int64_t* __restrict__ total, const int64_t* __restrict__ unit_start,
+    const int64_t* __restrict__ total, int64_t max_units, const int64_t* __restrict__ unit_start,
     int64_t* __restrict__ out) {
   __shared__ BlockUnits<C> bu;
   __shared__ int64_t s_w[C::waves];
-  if (block_x().index() * C::waves >= total[0]) return;
-  find_units<C>(offsets, unit_start, n, S, total[0], bu);
+  const auto mine = layout::block_units<C::waves>(block_x().index(), total[0], max_units);
+  if (mine.count <= 0) return;
+  find_units<C>(offsets, unit_start, n, S, mine, bu);
   auto thread = thread_x<C::block>();
   auto o = array(out, S);
   const int w = (int)wave_of_block<C::block>().index();
@@ -711,13 +712,13 @@ template <class C>
 __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
     const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
     const int64_t* __restrict__ offsets, int64_t S, const int64_t* __restrict__ total,
-    const int64_t* __restrict__ unit_start, uint64_t* __restrict__ status,
+    int64_t max_units, const int64_t* __restrict__ unit_start, uint64_t* __restrict__ status,
     WsHeader* __restrict__ hdr) {
   __shared__ BlockUnits<C> bu;
   __shared__ ScanShared sh;
-  const idx_t u0 = block_x().index() * C::waves;
-  if (u0 >= total[0]) return;
-  find_units<C>(offsets, unit_start, n, S, total[0], bu);
+  const auto mine = layout::block_units<C::waves>(block_x().index(), total[0], max_units);
+  if (mine.count <= 0) return;
+  find_units<C>(offsets, unit_start, n, S, mine, bu);
   auto thread = thread_x<C::block>();
   const int w = (int)wave_of_block<C::block>().index();
   if (w < bu.count && is_short(bu.ui[w])) {   // whole segments: nothing to publish or look up
@@ -725,8 +726,8 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
     uint32_t x[kShortRounds][4];
     load_short(in, bu.ui[w].begin, (int)len, x);
     auto run = array(out, 0).snd(bu.ui[w].begin);
-    auto mine = layout::wave_striped<1, kShortRounds>(array(&run[0], kShortLen).template group<4>(),
-                                                      0, Wave<1>{0, 1}, lane_of_wave());
+    auto groups = layout::wave_striped<1, kShortRounds>(
+        array(&run[0], kShortLen).template group<4>(), 0, Wave<1>{0, 1}, lane_of_wave());
     uint32_t carry = 0;
 #pragma unroll
     for (int r = 0; r < kShortRounds; ++r) {
@@ -735,7 +736,7 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
       x[r][3] += x[r][2];
       const uint32_t incl = wave::inclusive_add_u32(x[r][3]);
       const uint32_t ex = carry + incl - x[r][3];
-      auto g = mine.idx(r);
+      auto g = groups.idx(r);
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (g.pos(k) < len) g[k] = (int32_t)(x[r][k] + ex);
@@ -747,7 +748,7 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
 #pragma clang loop unroll(disable)
   for (int i = 0; i < bu.count; ++i) {
     if (is_short(bu.ui[i])) continue;
-    scan_unit<C>(in, out, bu.ui[i], u0 + i, status, polls, hdr, sh);
+    scan_unit<C>(in, out, bu.ui[i], mine.first + i, status, polls, hdr, sh);
     sync(thread);                          // sh is reused by the next unit
   }
 }
@@ -842,7 +843,7 @@ hipError_t launch_reduce(const int32_t* in, int64_t n, const int64_t* offsets, i
   if (units > 0 && many_short)
     hipLaunchKernelGGL(seg_reduce_short_kernel<C>,
                        dim3((unsigned)((units + C::waves - 1) / C::waves)), dim3(C::block), 0, s,
-                       in, n, offsets, S, w.total, w.unit_start, out);
+                       in, n, offsets, S, w.total, units, w.unit_start, out);
   else if (units > 0)
     hipLaunchKernelGGL(seg_reduce_kernel<C>, dim3((unsigned)units), dim3(C::block), 0, s, in, n,
                        offsets, S, w.total, w.unit_start, out);
@@ -863,7 +864,7 @@ hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, const int64_t
   if (mu > 0 && short_scan(n, S))
     hipLaunchKernelGGL(seg_scan_short_kernel<C>,
                        dim3((unsigned)((mu + C::waves - 1) / C::waves)), dim3(C::block), 0, s, in,
-                       out, n, offsets, S, w.total, w.unit_start, w.status, (WsHeader*)ws);
+                       out, n, offsets, S, w.total, mu, w.unit_start, w.status, (WsHeader*)ws);
   else if (mu > 0)
     hipLaunchKernelGGL(seg_scan_kernel<C>, dim3((unsigned)mu), dim3(C::block), 0, s, in, out, n,
                        offsets, S, w.total, w.unit_start, w.status, (WsHeader*)ws);

@@ -1,0 +1,89 @@
+"""The segmented forms that give a block one unit per wave: which units the
+blocks take, on the host, and offsets that run backwards, on the GPU.
+
+Such offsets give unspecified results, but the workspace is sized for the
+units of non-decreasing ones: a unit past them has no status word, and what
+it wrote would land in the unit prefix that other blocks read."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2305_03448_amd as desc
+import workloads
+from gpu_util import case, dev, needs_gpu, to_dev
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2305_03448_amd", "csrc")
+
+CHECK = r'''
+#include <cstdio>
+#include <vector>
+#include "layouts.hpp"
+using namespace desc;
+// Blocks of kW units cover the units of a call once, whatever the launched
+// bound, and none past it even when more are planned.
+template <int kW>
+static bool covers() {
+  for (idx_t bound = 0; bound <= 6 * kW; ++bound)
+    for (idx_t total = 0; total <= 12 * kW; ++total) {
+      std::vector<int> taken(bound, 0);
+      for (idx_t b = 0; b < (bound + kW - 1) / kW; ++b) {
+        const layout::BlockRange r = layout::block_units<kW>(b, total, bound);
+        for (int w = 0; w < r.count; ++w) {
+          if (r.first + w >= bound) return false;
+          ++taken[r.first + w];
+        }
+      }
+      for (idx_t u = 0; u < bound; ++u)
+        if (taken[u] != (u < total ? 1 : 0)) return false;
+    }
+  return true;
+}
+int main() {
+  const bool ok = covers<4>() && covers<8>() && covers<16>();
+  std::puts(ok ? "OK" : "FAIL");
+  return !ok;
+}
+'''
+
+
+def test_blocks_take_no_unit_past_the_bound(tmp_path):
+    src, exe = str(tmp_path / "c.cpp"), str(tmp_path / "c")
+    with open(src, "w") as f:
+        f.write(CHECK)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, src, "-o", exe], check=True)
+    assert subprocess.run([exe], capture_output=True, text=True, timeout=60).stdout == "OK\n"
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("S", [2049, 4098, 8195])
+def test_offsets_that_run_backwards(S):
+    """Every second segment is the whole array: S / 2 times the planned units.
+    The call ends, writes nothing beside its output, and the workspace serves
+    the next one."""
+    n = 300 * S
+    case(f"backward offsets S={S} n={n}")
+    x = workloads.int_uniform(n, seed=61)
+    xt = to_dev(x)
+    bad = torch.zeros(S + 1, dtype=torch.int64)
+    bad[1::2] = n
+    lengths = np.full(S, 300, np.int64)
+    off = workloads.offsets_from_lengths(lengths)
+    ws = torch.zeros(desc.desc_scan_segmented_i32_workspace(n, S), dtype=torch.uint8, device=dev())
+    buf = torch.full((n + 16,), -7, dtype=torch.int32, device=dev())
+    sums = torch.full((S + 16,), -7, dtype=torch.int64, device=dev())
+    wr = torch.zeros(desc.desc_reduce_segmented_i32_workspace(n, S), dtype=torch.uint8, device=dev())
+    for o in (bad, torch.from_numpy(off)):
+        ot = o.to(dev())
+        desc.desc_scan_segmented_i32(xt, ot, buf[8:8 + n], ws=ws)
+        desc.desc_reduce_segmented_i32(xt, ot, sums[8:8 + S], ws=wr)
+        torch.cuda.synchronize()
+    for b in (buf, sums):
+        assert (b[:8] == -7).all() and (b[-8:] == -7).all()
+    assert np.array_equal(buf[8:8 + n].cpu().numpy(), oracle.scan_segmented_i32(x, off))
+    assert np.array_equal(sums[8:8 + S].cpu().numpy(), oracle.reduce_segmented_i32(x, off))
