@@ -11,6 +11,14 @@
 namespace desc {
 namespace launch {
 
+// Whether a launch of `blocks` blocks of `threads` threads along x runs as
+// asked: the dispatch counts those threads in 32 bits, and a launch of more is
+// not refused but runs the count modulo 2^32 (2^32 + 512 threads ran one block
+// and returned success; exactly 2^32 returned an error).
+inline bool grid_fits(int64_t blocks, int64_t threads) {
+  return blocks <= (int64_t)0xFFFFFFFF / threads;
+}
+
 // Blocks of `kernel` (of `threads` threads) that fit the device at once: its
 // occupancy per CU times the CUs, per device, computed on first use
 // (`fallback_per_cu` if the occupancy query fails).

@@ -28,6 +28,8 @@
 // tile and barrier.
 // The kernel moves bit patterns only: NaN payloads, signed zeros and
 // subnormals pass unchanged.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "layouts.hpp"
@@ -142,6 +144,13 @@ hipError_t launch_transpose(const uint32_t* in, uint32_t* out, int64_t batch, in
   constexpr int T = C::t;
   if (any_shape<uint32_t>(in, out, rows, cols, T))
     return transpose_any<uint32_t>(in, out, batch, rows, cols, s);
+  // past 2^29 columns (2^30 of a 128-wide tile of 512 threads) 128 x 128 tiles
+  // of 256 threads, whose grid takes every column count the call accepts
+  using Wide = TransposeCfg<128, C::nt>;
+  if constexpr (!std::is_same_v<C, Wide>)
+    if (!launch::grid_fits((cols + T - 1) / T, C::block))
+      return launch_transpose<Wide>(in, out, batch, rows, cols, s);
+  if (!launch::grid_fits((cols + T - 1) / T, C::block)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)((cols + T - 1) / T), (unsigned)((rows + T - 1) / T),
                   (unsigned)batch);
   const bool vec = rows % 4 == 0 && cols % 4 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
@@ -329,10 +338,14 @@ __global__ __launch_bounds__(C::block) void transpose_any_kernel(const E* __rest
 // 10-15 us a launch by their latency alone: 2000 x 2000 words 17.4 -> 7.1 us,
 // 100 x 200 16-bit elements 16.5 -> 3.2, a batch of 12 1000 x 777 of them
 // 34.9 -> 10.4; and on unaligned matrices most of the time: 8191 x 16001
-// 16-bit elements 360 -> 167 us, 8191 x 8189 words 222 -> 129 us.
+// 16-bit elements 360 -> 167 us, 8191 x 8189 words 222 -> 129 us.  Its largest
+// tiles have 512 threads, so twice as many columns reach the end of a grid:
+// such a matrix keeps the 256-thread form.
 template <class E>
 bool any_shape(const void* in, const void* out, int64_t rows, int64_t cols, int T) {
   constexpr int kV = 16 / (int)sizeof(E);
+  constexpr int kLargest = sizeof(E) == 8 ? 64 : 128;
+  if (!launch::grid_fits((cols + kLargest - 1) / kLargest, 512)) return false;
   const bool whole =
       rows % T == 0 && cols % T == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
   return !whole && rows >= kV && cols >= kV;
@@ -387,6 +400,7 @@ hipError_t launch_transpose_elem(const void* in, void* out, int64_t batch, int64
   using C = TransposeCfgE<E, kT>;
   if (any_shape<E>(in, out, rows, cols, kT))
     return transpose_any<E>(in, out, batch, rows, cols, s);
+  if (!launch::grid_fits((cols + kT - 1) / kT, kBlock)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)((cols + kT - 1) / kT), (unsigned)((rows + kT - 1) / kT),
                   (unsigned)batch);
   const bool vec = rows % C::v == 0 && cols % C::v == 0 &&

@@ -1,0 +1,37 @@
+"""Calls whose block counts pass what one grid dimension takes in the form that
+is fastest for ordinary sizes.  A launch of 2^32 threads or more along x is not
+refused: it runs the count modulo 2^32, so a form may only be chosen where its
+grid fits."""
+import pytest
+import torch
+
+import paper_2305_03448_amd as desc
+from gpu_util import case, dev, needs_gpu
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+
+@pytest.fixture(autouse=True)
+def _release():
+    yield
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("elem,rows,cols", [(8, 2, (1 << 29) + 1), (4, 4, (1 << 30) + 1),
+                                            (2, 8, (1 << 30) + 1), (1, 16, (1 << 30) + 1),
+                                            (4, 1, (1 << 30) + 1)])
+def test_transpose_of_many_columns(elem, rows, cols):
+    case(f"transpose {elem}-byte {rows}x{cols}")
+    dtype = {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64}[elem]
+    # rows of random values whose period shares no factor with a tile
+    g = torch.Generator(device=dev()).manual_seed(81)
+    part = torch.randint(0, (1 << (8 * elem - 1)) - 1, (65521,), device=dev(), generator=g).to(dtype)
+    x = torch.empty(rows, cols, dtype=dtype, device=dev())
+    for r in range(rows):
+        x[r] = part.roll(r).repeat(-(-cols // part.numel()))[:cols]
+    y = torch.zeros(cols + 1, rows, dtype=dtype, device=dev())
+    y[cols] = 77                         # beside the result
+    desc.desc_transpose_batched(x, y[:cols])
+    for r in range(rows):
+        assert torch.equal(y[:cols, r], x[r])
+    assert bool((y[cols] == 77).all())
