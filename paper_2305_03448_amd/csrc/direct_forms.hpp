@@ -12,7 +12,10 @@
 // (K = 64: 13.2 against 17.2 us), and tiles up to 32 x 32 read too little to
 // disturb each other at any K measured.
 #pragma once
+#include <cmath>
+
 #include "gemm_direct.hpp"
+#include "launch.hpp"
 
 namespace desc {
 namespace {
@@ -47,12 +50,19 @@ hipError_t launch_direct(const GemmProblemF32& g, hipStream_t s) {
 struct DirectForm {
   int bm, bn, cols;      // tile; columns one load holds (N must reach them)
   double ns_per_k;
+  int threads;           // a block's
   hipError_t (*launch)(const GemmProblemF32&, hipStream_t);
+  // A row of C holds one load, and the grid counts the call's threads: N of up
+  // to 16 takes 4 threads a row in 64 x 16 tiles, 2^32 at 2^30 rows, where the
+  // LDS-staged 128-row tiles stay at two a row.
+  bool takes(int64_t M, int64_t N) const {
+    return N >= cols && launch::grid_fits(((M + bm - 1) / bm) * ((N + bn - 1) / bn), threads);
+  }
 };
 template <bool kSplit, int kFM, int kFN, int kWM, int kWN, int kWK, int kDepth>
 constexpr DirectForm direct(double ns_per_k) {
   using C = DirectCfg<kFM, kFN, kWM, kWN, kWK, kDepth>;
-  return {C::bm, C::bn, C::fn, ns_per_k, launch_direct<C, kSplit>};
+  return {C::bm, C::bn, C::fn, ns_per_k, C::threads, launch_direct<C, kSplit>};
 }
 
 // A call's time as rounds of 256 tiles, each K steps and the start and end
@@ -76,22 +86,22 @@ inline double later_rounds_us(int bm, int bn, int64_t K) {
   return K < 100 ? 2.0 : K < 512 ? 5.0 : 1.0;
 }
 
-// The fastest of `count` direct forms by that estimate (the last one, 16 x 16,
-// takes any N).
-inline const DirectForm& best_direct(const DirectForm* forms, int count, int64_t M, int64_t N,
+// The fastest of `count` direct forms by that estimate, or null (*us infinite)
+// where none takes the call.
+inline const DirectForm* best_direct(const DirectForm* forms, int count, int64_t M, int64_t N,
                                      int64_t K, bool fp32, double* us) {
-  const DirectForm* best = &forms[count - 1];
-  *us = 1e300;
+  const DirectForm* best = nullptr;
+  *us = INFINITY;
   for (int i = 0; i < count; ++i) {
     const DirectForm& f = forms[i];
-    if (N < f.cols) continue;
+    if (!f.takes(M, N)) continue;
     double ends = 1.5 + f.bm * f.bn / 8192.0;
     if (fp32 && ((M + f.bm - 1) / f.bm) * ((N + f.bn - 1) / f.bn) > 256)
       ends += later_rounds_us(f.bm, f.bn, K);
     const double t = rounds_us(M, N, K, f.bm, f.bn, f.ns_per_k, ends);
     if (t < *us) { best = &f; *us = t; }
   }
-  return *best;
+  return best;
 }
 
 }  // namespace

@@ -167,7 +167,7 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
   if (cfg == kClamped) return launch_gemm_c<Staged>(g, s);
   if (cfg >= kByShape) {
     const bool strides = lda <= kDirectMaxLd && ldb <= kDirectMaxLd;
-    if (cfg > kByShape && strides && N >= kDirect[cfg - kByShape - 1].cols)
+    if (cfg > kByShape && strides && kDirect[cfg - kByShape - 1].takes(M, N))
       return kDirect[cfg - kByShape - 1].launch(g, s);
     // The LDS-staged 128 x 128 tile, up to three blocks a CU, is the faster
     // one per unit of K once several rounds of its tiles run: 67 ns a round
@@ -177,11 +177,12 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     // round nearly empty: 260 against 171 us in 96 x 64 direct tiles).
     if (strides) {
       double us = 0;
-      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, true, &us);
+      const DirectForm* d = best_direct(kDirect, kDirectForms, M, N, K, true, &us);
       const double tiles = (double)((M + 127) / 128) * (double)((N + 127) / 128);
       const double ns = 58.0 + 9.0 / (tiles <= 256 ? 1.0 : tiles / 256);
-      if (!gemm_f32::clamped_tile<Staged>(g) || us <= rounds_us(M, N, K, 128, 128, ns, K < 512 ? 4.0 : 2.0))
-        return d.launch(g, s);
+      const bool staged_ok = gemm_f32::clamped_tile<Staged>(g);
+      if (d && (!staged_ok || us <= rounds_us(M, N, K, 128, 128, ns, K < 512 ? 4.0 : 2.0)))
+        return d->launch(g, s);
     }
     // whole tiles of aligned rows keep the form without clamps (4096^3: 941
     // against 956 us)

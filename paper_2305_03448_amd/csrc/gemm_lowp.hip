@@ -1122,11 +1122,11 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
     const double dma = dma_ok && K > 0 ? split_dma_us(M, N, K) : INFINITY;
     if (K > 0 && lda <= kDirectMaxLd && ldb <= kDirectMaxLd) {
       const GemmProblemF32 g{A, lda, B, ldb, Cm, ldc, M, N, K};
-      if (cfg > kByShape && N >= kDirect[cfg - kByShape - 1].cols)
+      if (cfg > kByShape && kDirect[cfg - kByShape - 1].takes(M, N))
         return kDirect[cfg - kByShape - 1].launch(g, s);
       double us = 0;
-      const DirectForm& d = best_direct(kDirect, kDirectForms, M, N, K, false, &us);
-      if (us <= fused && us <= dma) return d.launch(g, s);
+      const DirectForm* d = best_direct(kDirect, kDirectForms, M, N, K, false, &us);
+      if (d && us <= fused && us <= dma) return d->launch(g, s);
     }
     cfg = dma < fused ? kBf16Dma : fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;
   }

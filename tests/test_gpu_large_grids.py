@@ -35,3 +35,13 @@ def test_transpose_of_many_columns(elem, rows, cols):
     for r in range(rows):
         assert torch.equal(y[:cols, r], x[r])
     assert bool((y[cols] == 77).all())
+
+
+@pytest.mark.parametrize("M", [1 << 30, (1 << 30) + (1 << 20) + 3])
+def test_f32_product_of_many_rows(M):
+    case(f"gemm f32 {M}x1x1")
+    A = (torch.arange(M, dtype=torch.int32, device=dev()) % 1021).float().view(M, 1)
+    C = torch.full((M + 1, 1), -7.0, device=dev())
+    desc.desc_gemm(A, torch.full((1, 1), 3.0, device=dev()), C[:M], mode="f32")
+    assert torch.equal(C[:M], A * 3)     # integers: exact
+    assert float(C[M]) == -7.0
