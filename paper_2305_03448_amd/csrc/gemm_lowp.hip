@@ -772,8 +772,10 @@ template <class C>
 hipError_t launch_fp8_once(const float* A, int64_t M, int64_t lda, uint8_t* qa, int64_t Mp,
                            float* sa, const float* B, int64_t N, int64_t ldb, uint8_t* qb,
                            int64_t Np, float* sb, int64_t K, int64_t Kp, hipStream_t s) {
-  hipLaunchKernelGGL(fp8_once_kernel<C>, dim3((unsigned)(Np / kStripCols + Mp / kOnceWaves)),
-                     dim3(kOnceBlock), 0, s, A, M, lda, qa, Mp, sa, B, N, ldb, qb, Np, sb, K, Kp);
+  const int64_t blocks = Np / kStripCols + Mp / kOnceWaves;
+  if (!launch::grid_fits(blocks, kOnceBlock)) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(fp8_once_kernel<C>, dim3((unsigned)blocks), dim3(kOnceBlock), 0, s, A, M, lda,
+                     qa, Mp, sa, B, N, ldb, qb, Np, sb, K, Kp);
   return hipGetLastError();
 }
 
@@ -1188,22 +1190,27 @@ hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     return launch_fp8_once<decltype(cfg_tag)>(A, M, lda, qa, L.Mp, sa, B, N, ldb, qb, L.Np, sb, K,
                                               L.Kp, s);
   };
+  // the product runs only over codes that were written: a pre-pass that is not
+  // launched (2^26 rows; 2^24 beyond K = 2048, a block a row) ends the call
+  hipError_t pre;
   if (K > 0 && L.Kp <= 2048) {
-    (void)(L.Kp <= 512    ? once(OnceCfg<4>{})
-           : L.Kp <= 1024 ? once(OnceCfg<8>{})
-                          : once(OnceCfg<16>{}));
+    pre = L.Kp <= 512    ? once(OnceCfg<4>{})
+          : L.Kp <= 1024 ? once(OnceCfg<8>{})
+                         : once(OnceCfg<16>{});
   } else {
     auto two = [&](auto nt) {
       const int64_t S = colmax_slices(K, N), rows_per = (K + S - 1) / S;
       const int64_t cblocks = (L.Np + 4 * kBlock - 1) / (4 * kBlock);
+      if (!launch::grid_fits(cblocks * S + L.Mp, kBlock)) return hipErrorInvalidConfiguration;
       hipLaunchKernelGGL(fp8_prepass_kernel<nt()>, dim3((unsigned)(cblocks * S + L.Mp)),
                          dim3(kBlock), 0, s, A, M, K, lda, qa, L.Mp, L.Kp, L.Kp, sa, f4_ok(A, lda),
                          B, N, ldb, rows_per, part, L.Np, f4_ok(B, ldb), cblocks, S);
       return launch_cols_t<nt()>(B, K, N, ldb, part, S, L.Np, qb, L.Np, L.Kp, L.Kp, sb,
                                  f4_ok(B, ldb), true, s);
     };
-    (void)(bytes > (int64_t(256) << 20) ? two(std::true_type{}) : two(std::false_type{}));
+    pre = bytes > (int64_t(256) << 20) ? two(std::true_type{}) : two(std::false_type{});
   }
+  if (pre != hipSuccess) return pre;
   NtOperands p{{qa, nullptr}, {qb, nullptr}, L.Kp, Cm, ldc, M, N, sa, sb};
   if (cfg == kFp8Dma) {
     if (dma_fits(p.row_bytes, ldc))

@@ -45,3 +45,21 @@ def test_f32_product_of_many_rows(M):
     desc.desc_gemm(A, torch.full((1, 1), 3.0, device=dev()), C[:M], mode="f32")
     assert torch.equal(C[:M], A * 3)     # integers: exact
     assert float(C[M]) == -7.0
+
+
+def test_fp8_product_whose_pre_pass_is_not_launched():
+    """2^26 rows of K up to 2048: more blocks of 512 threads than a grid counts,
+    eight rows to a block.  The call says so, or its result is right: never a
+    product of codes that were not written."""
+    M, N, K = 1 << 26, 1, 1
+    case(f"gemm fp8 {M}x{N}x{K}")
+    A = torch.full((M, K), 3.0, device=dev())
+    B = torch.full((K, N), 2.0, device=dev())
+    C = torch.full((M, N), -7.0, device=dev())
+    ws = torch.zeros(desc.desc_gemm_workspace("fp8", M, N, K), dtype=torch.uint8, device=dev())
+    try:
+        desc.desc_gemm(A, B, C, mode="fp8", ws=ws)
+    except desc.DescError:
+        return
+    # 448 * 448 scaled by 3 / 448 and 2 / 448: three roundings of 2^-24 each
+    assert bool(((C - 6.0).abs() <= 6.0 * 2.0 ** -21).all())
