@@ -576,15 +576,19 @@ __global__ __launch_bounds__(kBlock) void quant_cols_t_kernel(const float* __res
                                                               uint8_t* __restrict__ qt,
                                                               int64_t n_out, int64_t k_out,
                                                               int64_t ldq,
-                                                              float* __restrict__ scale) {
+                                                              float* __restrict__ scale,
+                                                              uint32_t k_blocks) {
   constexpr int kR = kEncodeRows, kWaves = kBlock / kWave;
   constexpr int kCols = 32 * (kWaves / kW), kGroups = kBlock / kCols;
   __shared__ float pmax[kGroups][kCols];
   auto thread = thread_x<kBlock>();
   const int w = (int)wave_of_block<kBlock>().index(), lane = (int)lane_of_wave().index();
   const int c4 = 32 * (w / kW) + 4 * (lane % 8);          // the thread's first column
-  const idx_t n0 = block_y().index() * kCols, n = n0 + c4;
-  const idx_t k = ((block_x().index() * kW + w % kW) * 8 + lane / 8) * kR;   // and first k
+  // k blocks of a column block follow each other; one dimension, since a second
+  // one would end at 65535 of them (2^21 columns)
+  const uint32_t blk = (uint32_t)block_x().index();
+  const idx_t n0 = (idx_t)(blk / k_blocks) * kCols, n = n0 + c4;
+  const idx_t k = ((blk % k_blocks * kW + w % kW) * 8 + lane / 8) * kR;      // and first k
   f32x4 v[kR];
   load_cols<kR, kNt>(B, K, N, ldb, k, n, n0 + kCols <= N, v);
   {
@@ -627,20 +631,22 @@ hipError_t launch_cols_t(const float* B, int64_t K, int64_t N, int64_t ldb, cons
                          int64_t nslices, int64_t ldp, uint8_t* qt, int64_t n_out, int64_t k_out,
                          int64_t ldq, float* scale, bool vec_in, bool vec_out, hipStream_t s) {
   const int64_t tk = (k_out + 63) / 64, tn = (n_out + 63) / 64;
-  if (tk * tn <= 2048 || (tk * tn <= 8192 && vec_in))
+  if (tk * tn <= 2048 || (tk * tn <= 8192 && vec_in)) {
     hipLaunchKernelGGL(quant_cols_tile_kernel, dim3((unsigned)tk, (unsigned)tn), dim3(kBlock), 0, s,
                        B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, vec_in,
                        vec_out);
-  else if (k_out >= 512)
-    hipLaunchKernelGGL((quant_cols_t_kernel<4, kNt>),
-                       dim3((unsigned)((k_out + 511) / 512), (unsigned)((n_out + 31) / 32)),
-                       dim3(kBlock), 0, s, B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq,
-                       scale);
+    return hipGetLastError();
+  }
+  const bool wide = k_out >= 512;         // blocks of 512 k x 32 columns, or 128 x 128
+  const int64_t kb = wide ? (k_out + 511) / 512 : (k_out + 127) / 128;
+  const int64_t blocks = kb * (wide ? (n_out + 31) / 32 : (n_out + 127) / 128);
+  if (!launch::grid_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
+  if (wide)
+    hipLaunchKernelGGL((quant_cols_t_kernel<4, kNt>), dim3((unsigned)blocks), dim3(kBlock), 0, s, B,
+                       K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, (uint32_t)kb);
   else
-    hipLaunchKernelGGL((quant_cols_t_kernel<1, kNt>),
-                       dim3((unsigned)((k_out + 127) / 128), (unsigned)((n_out + 127) / 128)),
-                       dim3(kBlock), 0, s, B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq,
-                       scale);
+    hipLaunchKernelGGL((quant_cols_t_kernel<1, kNt>), dim3((unsigned)blocks), dim3(kBlock), 0, s, B,
+                       K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, (uint32_t)kb);
   return hipGetLastError();
 }
 

@@ -11,6 +11,9 @@ from gpu_util import case, dev, needs_gpu
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
 
+WIDE = 65535 * 32 + 33               # columns: more than 65535 blocks of 32
+
+
 @pytest.fixture(autouse=True)
 def _release():
     yield
@@ -63,3 +66,42 @@ def test_fp8_product_whose_pre_pass_is_not_launched():
         return
     # 448 * 448 scaled by 3 / 448 and 2 / 448: three roundings of 2^-24 each
     assert bool(((C - 6.0).abs() <= 6.0 * 2.0 ** -21).all())
+
+
+def _e4m3(shape, seed):
+    """448 / 2^i (i = 0..2), of either sign, or 0, with 448 in row K // 2 (or
+    column K // 2): unit scales, and products and short sums exact in FP32."""
+    g = torch.Generator(device=dev()).manual_seed(seed)
+    s = torch.randint(-1, 2, shape, device=dev(), generator=g, dtype=torch.int8).float()
+    return 448 * s / 2.0 ** torch.randint(0, 3, shape, device=dev(), generator=g, dtype=torch.int8)
+
+
+def test_fp8_product_of_many_columns():
+    M, N, K = 1, WIDE, 2049
+    case(f"gemm fp8 {M}x{N}x{K}")
+    A, part = _e4m3((M, K), 81), _e4m3((K, 1023), 82)
+    A[:, K // 2] = 448
+    part[K // 2] = 448
+    B = part.repeat(1, -(-N // 1023))[:, :N].contiguous()
+    want = (A.double() @ part.double()).float().repeat(1, -(-N // 1023))[:, :N]
+    C = torch.full((M, N), -7.0, device=dev())
+    desc.desc_gemm(A, B, C, mode="fp8")
+    assert torch.equal(C, want)
+
+
+@pytest.mark.parametrize("K", [511, 512])
+def test_fp8_column_codes_of_many_columns(K):
+    N = WIDE
+    case(f"quant e4m3 cols {K}x{N}")
+    g = torch.Generator(device=dev()).manual_seed(83)
+    part = torch.randn(K, 1023, device=dev(), generator=g)
+    B = part.repeat(1, -(-N // 1023))[:, :N].contiguous()
+    q = torch.full((N, K), 0x55, dtype=torch.uint8, device=dev())
+    s = torch.full((N,), -7.0, device=dev())
+    desc.desc_quant_e4m3_cols(B, q, s)
+    want_q = torch.empty(1023, K, dtype=torch.uint8, device=dev())
+    want_s = torch.empty(1023, device=dev())
+    desc.desc_quant_e4m3_rows(part.t().contiguous(), want_q, want_s)
+    for at in range(0, N, 1023):
+        n = min(1023, N - at)
+        assert torch.equal(q[at:at + n], want_q[:n]) and torch.equal(s[at:at + n], want_s[:n]), at
