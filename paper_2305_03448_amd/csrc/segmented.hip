@@ -506,60 +506,29 @@ struct ScanShared {
   uint32_t prefix;     // the unit's exclusive prefix
 };
 
-// One unit of the segmented scan (u its index).
+// A wave's part of a unit scanned in registers, from its first element on.
 template <class C>
-__device__ __forceinline__ void scan_unit(const int32_t* __restrict__ in,
-                                          int32_t* __restrict__ out, const UnitInfo& ui, idx_t u,
-                                          uint64_t* __restrict__ status, uint32_t polls,
-                                          WsHeader* __restrict__ hdr, ScanShared& sh) {
-  constexpr int kBlock = C::block, kWaves = C::waves, kRounds = C::rounds, kUnit = C::unit;
-  static_assert(kWaves <= 16, "wave totals fit ScanShared");
-  auto thread = thread_x<kBlock>();
-  auto wv = wave_of_block<kBlock>();
-  auto lane = lane_of_wave();
-  uint32_t x[kRounds][4];
-  load_unit<C>(in, ui, x);
-
-  uint32_t lsum = 0;
-#pragma unroll
-  for (int r = 0; r < kRounds; ++r) lsum += x[r][0] + x[r][1] + x[r][2] + x[r][3];
-  const uint32_t wsum = wave::sum_u32(lsum);
-  if (lane.index() == 0) sh.wtot[wv.index()] = wsum;
-  sync(thread);
-  uint32_t wex = 0, agg = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t v = sh.wtot[w];
-    wex += (w < wv.index()) ? v : 0u;
-    agg += v;
-  }
-  auto st = array(status, u + 1);
-  if (wv.index() == 0) {
-    uint32_t excl = 0;
-    if (ui.j == 0) {
-      if (lane.index() == 0) store_status(&st[u], pack(kFlagPrefix, agg));
-    } else {
-      if (lane.index() == 0) store_status(&st[u], pack(kFlagAggregate, agg));
-      excl = seg_look_back(status, u, ui.j, polls, hdr);
-      if (lane.index() == 0) store_status(&st[u], pack(kFlagPrefix, excl + agg));
-    }
-    if (lane.index() == 0) sh.prefix = excl;
-  }
+__device__ __forceinline__ void scan_wave(uint32_t (&x)[C::rounds][4]) {
+  constexpr int kRounds = C::rounds;
   uint32_t carry = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     x[r][1] += x[r][0];
     x[r][2] += x[r][1];
     x[r][3] += x[r][2];
-    const uint32_t t = x[r][3];
-    const uint32_t incl = wave::inclusive_add_u32(t);
-    const uint32_t ex = carry + incl - t;
+    const uint32_t incl = wave::inclusive_add_u32(x[r][3]);
+    const uint32_t ex = carry + incl - x[r][3];
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[r][k] += ex;
     carry += wave::lane_read_u32(incl, kWave - 1);
   }
-  sync(thread);
-  const uint32_t add = sh.prefix + wex;
+}
+
+// Those values, `add` before each, to the unit's positions of `out`.
+template <class C>
+__device__ __forceinline__ void store_unit(int32_t* __restrict__ out, const UnitInfo& ui,
+                                           const uint32_t (&x)[C::rounds][4], uint32_t add) {
+  constexpr int kWaves = C::waves, kRounds = C::rounds, kUnit = C::unit;
   auto unit = array(out, 0).snd(ui.begin);
   const uint32_t ot = opaque_thread();
   const Wave<kWaves> owv{(idx_t)(ot / kWave), kWaves};
@@ -597,15 +566,58 @@ __device__ __forceinline__ void scan_unit(const int32_t* __restrict__ in,
   }
 }
 
+// One unit of the segmented scan (u its index).
 template <class C>
-__global__ __launch_bounds__(C::block) void seg_scan_kernel(const int32_t* __restrict__ in,
-                                                          int32_t* __restrict__ out, int64_t n,
-                                                          const int64_t* __restrict__ offsets,
-                                                          int64_t S,
-                                                          const int64_t* __restrict__ total,
-                                                          const int64_t* __restrict__ unit_start,
-                                                          uint64_t* __restrict__ status,
-                                                          WsHeader* __restrict__ hdr) {
+__device__ __forceinline__ void scan_unit(const int32_t* __restrict__ in,
+                                          int32_t* __restrict__ out, const UnitInfo& ui, idx_t u,
+                                          uint64_t* __restrict__ status, uint32_t polls,
+                                          WsHeader* __restrict__ hdr, ScanShared& sh) {
+  constexpr int kBlock = C::block, kWaves = C::waves, kRounds = C::rounds;
+  static_assert(kWaves <= 16, "wave totals fit ScanShared");
+  auto thread = thread_x<kBlock>();
+  auto wv = wave_of_block<kBlock>();
+  auto lane = lane_of_wave();
+  uint32_t x[kRounds][4];
+  load_unit<C>(in, ui, x);
+
+  uint32_t lsum = 0;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) lsum += x[r][0] + x[r][1] + x[r][2] + x[r][3];
+  const uint32_t wsum = wave::sum_u32(lsum);
+  if (lane.index() == 0) sh.wtot[wv.index()] = wsum;
+  sync(thread);
+  uint32_t wex = 0, agg = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const uint32_t v = sh.wtot[w];
+    wex += (w < wv.index()) ? v : 0u;
+    agg += v;
+  }
+  auto st = array(status, u + 1);
+  if (wv.index() == 0) {
+    uint32_t excl = 0;
+    if (ui.j == 0) {
+      if (lane.index() == 0) store_status(&st[u], pack(kFlagPrefix, agg));
+    } else {
+      if (lane.index() == 0) store_status(&st[u], pack(kFlagAggregate, agg));
+      excl = seg_look_back(status, u, ui.j, polls, hdr);
+      if (lane.index() == 0) store_status(&st[u], pack(kFlagPrefix, excl + agg));
+    }
+    if (lane.index() == 0) sh.prefix = excl;
+  }
+  scan_wave<C>(x);
+  sync(thread);
+  const uint32_t add = sh.prefix + wex;
+  store_unit<C>(out, ui, x, add);
+}
+
+// Eight rounds take 64 registers, which is two blocks of 1024 threads on a CU.
+template <class C>
+__global__ __launch_bounds__(C::block) __attribute__((amdgpu_waves_per_eu(C::rounds == 8 ? 8 : 1)))
+void seg_scan_kernel(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
+                     const int64_t* __restrict__ offsets, int64_t S,
+                     const int64_t* __restrict__ total, const int64_t* __restrict__ unit_start,
+                     uint64_t* __restrict__ status, WsHeader* __restrict__ hdr) {
   __shared__ ScanShared sh;
   UnitInfo ui;
   if (!unit_info<C>(offsets, unit_start, n, S, total[0], &ui)) return;
@@ -621,8 +633,13 @@ __global__ __launch_bounds__(C::block) void seg_scan_kernel(const int32_t* __res
 // about 4 us with 8 blocks a CU, 50-60 us for 16384 segments).  Here a block
 // takes one unit per wave: the waves look their units up side by side, each
 // wave whose unit is a whole segment of at most kShortLen elements reduces or
-// scans it alone, and then the block works through its other units in order,
-// as a block per unit would.
+// scans it alone, and then the block works through its other units.  A reduce
+// takes them in order, as a block per unit would.  A scan may not where a
+// segment has several units: a unit published after an earlier one's look-back
+// would make every block wait for the one before it (one segment of 4 M
+// elements among 4095 short ones: 891 us, 27 with a block per unit; of 20 M
+// among 16383: 4440 and 287).  Then the block first publishes the sums of all its
+// units, looks back once, and reads the units again to write them (21 and 57 us).
 constexpr int kShortRounds = 4;
 constexpr int kShortLen = 256 * kShortRounds;
 
@@ -645,11 +662,31 @@ __device__ __forceinline__ void load_short(const int32_t* in, idx_t begin, int l
     if (256 * r < len) load_group<false>(&run[0], (int)mine.idx(r).pos(0), len, x[r]);
 }
 
+// The partial sums of a block's units, by unit and wave, and their prefixes.
+template <class C>
+struct RunShared {
+  uint32_t part[C::waves][C::waves];
+  uint32_t prefix[C::waves];
+};
+
 // This block's units, one per wave, in LDS.
+constexpr uint8_t kShortUnit = 0, kWholeUnit = 1, kRunUnit = 2;   // kRunUnit: others wait for it
 template <class C>
 struct BlockUnits {
   UnitInfo ui[C::waves];
   int count;
+  __attribute__((aligned(4))) uint8_t kind[C::waves];
+  // Whether some unit is not a short one, and whether one past the first is a
+  // kRunUnit: a word read for four units.
+  __device__ bool any_long() const { return kinds(0x03030303u, 0x03030303u); }
+  __device__ bool any_run() const { return kinds(0x02020200u, 0x02020202u); }
+  __device__ bool kinds(uint32_t first, uint32_t others) const {
+    const uint32_t* k = (const uint32_t*)kind;
+    uint32_t found = k[0] & first;
+#pragma unroll
+    for (int i = 1; i < C::waves / 4; ++i) found |= k[i] & others;
+    return found != 0;
+  }
 };
 __device__ __forceinline__ bool is_short(const UnitInfo& ui) {
   return ui.single && ui.len <= kShortLen;
@@ -665,11 +702,74 @@ __device__ __forceinline__ void find_units(const int64_t* offsets, const int64_t
     const layout::SegUnit su =
         layout::seg_unit_of(array(offsets, S + 1), array(unit_start, S + 1), n, C::unit, u,
                             wave_owner(unit_start, S, u));
-    if (lane_of_wave().index() == 0)
-      bu.ui[w] = UnitInfo{su.seg, su.j, su.begin, su.len, su.single};
+    const UnitInfo ui{su.seg, su.j, su.begin, su.len, su.single};
+    if (lane_of_wave().index() == 0) {
+      bu.ui[w] = ui;
+      bu.kind[w] = is_short(ui) ? kShortUnit : ui.single ? kWholeUnit : kRunUnit;
+    }
+  } else if (lane_of_wave().index() == 0) {
+    bu.kind[w] = kShortUnit;
   }
   if (thread.index() == 0) bu.count = mine.count;
   sync(thread);
+}
+
+// The block's units but the short ones (the first is unit u0), with one
+// look-back: only the first unit can have its predecessor in another block.
+template <class C>
+__device__ __forceinline__ void scan_run(const int32_t* __restrict__ in, int32_t* __restrict__ out,
+                                         const BlockUnits<C>& bu, idx_t u0,
+                                         uint64_t* __restrict__ status, uint32_t polls,
+                                         WsHeader* __restrict__ hdr, RunShared<C>& sh) {
+  constexpr int kWaves = C::waves, kRounds = C::rounds;
+  auto thread = thread_x<C::block>();
+  const int w = (int)wave_of_block<C::block>().index(), lane = (int)lane_of_wave().index();
+#pragma clang loop unroll(disable)
+  for (int i = 0; i < bu.count; ++i) {
+    if (bu.kind[i] == kShortUnit) continue;
+    uint32_t x[kRounds][4];
+    load_unit<C>(in, bu.ui[i], x);
+    uint32_t sum = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) sum += x[r][0] + x[r][1] + x[r][2] + x[r][3];
+    sum = wave::sum_u32(sum);
+    if (lane == 0) sh.part[i][w] = sum;
+  }
+  sync(thread);
+  if (w == 0) {                               // lane i: unit i
+    auto st = array(status, u0 + bu.count);
+    const bool mine = lane < bu.count && bu.kind[lane] != kShortUnit;
+    const idx_t j = mine ? bu.ui[lane].j : 0;
+    uint32_t sum = 0;
+    if (mine) {
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) sum += sh.part[lane][v];
+      store_status(&st[u0 + lane], pack(j == 0 ? kFlagPrefix : kFlagAggregate, sum));
+    }
+    uint32_t before = bu.ui[0].j > 0 ? seg_look_back(status, u0, bu.ui[0].j, polls, hdr) : 0u;
+    uint32_t excl = 0;
+    for (int i = 0; i < bu.count; ++i) {
+      if (bu.ui[i].j == 0) before = 0;
+      if (lane == i) excl = before;
+      before += wave::lane_read_u32(sum, i);
+    }
+    if (mine) {
+      if (j > 0) store_status(&st[u0 + lane], pack(kFlagPrefix, excl + sum));
+      sh.prefix[lane] = excl;
+    }
+  }
+  sync(thread);
+#pragma clang loop unroll(disable)
+  for (int i = 0; i < bu.count; ++i) {
+    if (bu.kind[i] == kShortUnit) continue;
+    uint32_t x[kRounds][4];
+    load_unit<C>(in, bu.ui[i], x);
+    uint32_t add = sh.prefix[i];
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) add += v < w ? sh.part[i][v] : 0u;
+    scan_wave<C>(x);
+    store_unit<C>(out, bu.ui[i], x, add);
+  }
 }
 
 template <class C>
@@ -685,7 +785,7 @@ __global__ __launch_bounds__(C::block) void seg_reduce_short_kernel(
   auto thread = thread_x<C::block>();
   auto o = array(out, S);
   const int w = (int)wave_of_block<C::block>().index();
-  if (w < bu.count && is_short(bu.ui[w])) {
+  if (w < mine.count && bu.kind[w] == kShortUnit) {
     uint32_t x[kShortRounds][4];
     load_short(in, bu.ui[w].begin, (int)bu.ui[w].len, x);
     int64_t acc = 0;
@@ -696,9 +796,10 @@ __global__ __launch_bounds__(C::block) void seg_reduce_short_kernel(
     acc = wave::sum_i64(acc);
     if (lane_of_wave().index() == 0) o[bu.ui[w].seg] = acc;
   }
+  if (!bu.any_long()) return;
 #pragma clang loop unroll(disable)
   for (int i = 0; i < bu.count; ++i) {
-    if (is_short(bu.ui[i])) continue;
+    if (bu.kind[i] == kShortUnit) continue;
     const int64_t t = reduce_unit<C>(in, bu.ui[i], s_w);
     if (thread.index() == 0) {
       if (bu.ui[i].single) o[bu.ui[i].seg] = t;
@@ -715,13 +816,16 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
     int64_t max_units, const int64_t* __restrict__ unit_start, uint64_t* __restrict__ status,
     WsHeader* __restrict__ hdr) {
   __shared__ BlockUnits<C> bu;
-  __shared__ ScanShared sh;
+  __shared__ union {
+    ScanShared one;
+    RunShared<C> run;
+  } sh;
   const auto mine = layout::block_units<C::waves>(block_x().index(), total[0], max_units);
   if (mine.count <= 0) return;
   find_units<C>(offsets, unit_start, n, S, mine, bu);
   auto thread = thread_x<C::block>();
   const int w = (int)wave_of_block<C::block>().index();
-  if (w < bu.count && is_short(bu.ui[w])) {   // whole segments: nothing to publish or look up
+  if (w < mine.count && bu.kind[w] == kShortUnit) {   // whole segments: nothing to publish or look up
     const idx_t len = bu.ui[w].len;
     uint32_t x[kShortRounds][4];
     load_short(in, bu.ui[w].begin, (int)len, x);
@@ -743,12 +847,17 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
       carry += wave::lane_read_u32(incl, kWave - 1);
     }
   }
+  if (!bu.any_long()) return;
   const uint32_t polls = max_polls(
       __hip_atomic_load(&hdr->wait_limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  if (bu.any_run()) {
+    scan_run<C>(in, out, bu, mine.first, status, polls, hdr, sh.run);
+    return;
+  }
 #pragma clang loop unroll(disable)
   for (int i = 0; i < bu.count; ++i) {
-    if (is_short(bu.ui[i])) continue;
-    scan_unit<C>(in, out, bu.ui[i], mine.first + i, status, polls, hdr, sh);
+    if (bu.kind[i] == kShortUnit) continue;
+    scan_unit<C>(in, out, bu.ui[i], mine.first + i, status, polls, hdr, sh.one);
     sync(thread);                          // sh is reused by the next unit
   }
 }

@@ -87,3 +87,57 @@ def test_offsets_that_run_backwards(S):
         assert (b[:8] == -7).all() and (b[-8:] == -7).all()
     assert np.array_equal(buf[8:8 + n].cpu().numpy(), oracle.scan_segmented_i32(x, off))
     assert np.array_equal(sums[8:8 + S].cpu().numpy(), oracle.reduce_segmented_i32(x, off))
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("S", [2048, 4099])
+@pytest.mark.parametrize("runs", [1, 3, 50])
+def test_long_segments_among_short_ones(S, runs):
+    """A few long segments between segments of 0 to 6 elements: several units of
+    one segment in a block, segments that straddle blocks, and the wait limit
+    not reached."""
+    g = workloads.rng(67)
+    lengths = g.integers(0, 7, S)
+    at = (np.arange(runs) * (S // runs) + 1) % S
+    lengths[at] = 2_000_000 // runs + np.arange(runs)
+    off = workloads.offsets_from_lengths(np.asarray(lengths, np.int64))
+    n = int(off[-1])
+    x = workloads.int_uniform(n, seed=71)
+    case(f"{runs} long segments among S={S} n={n}")
+    xt, ot = to_dev(x, 1), to_dev(off)
+    ws = torch.zeros(desc.desc_scan_segmented_i32_workspace(n, S), dtype=torch.uint8, device=dev())
+    want = oracle.scan_segmented_i32(x, off)
+    for rep in range(3):
+        y = torch.full((n,), -5, dtype=torch.int32, device=dev())
+        desc.desc_scan_segmented_i32(xt, ot, y, ws=ws)
+        assert np.array_equal(y.cpu().numpy(), want)
+    assert desc.workspace_status(ws) == 0
+
+
+@pytest.mark.gpu
+@needs_gpu
+def test_one_long_segment_does_not_chain_the_blocks():
+    """The units of a long segment are published side by side whatever form the
+    number of segments selects: at 2047 a block per unit, from 2048 several units
+    a block.  In turn they take over 30 times as long, side by side about the
+    same; 5 is asked."""
+    n, times = 1 << 22, []
+    for S in (2047, 4096):
+        off = torch.zeros(S + 1, dtype=torch.int64)
+        off[1:] = n - 3 * torch.arange(S - 1, -1, -1)
+        x = torch.ones(n, dtype=torch.int32, device=dev())
+        y, ot = torch.empty_like(x), off.to(dev())
+        ws = torch.zeros(desc.desc_scan_segmented_i32_workspace(n, S), dtype=torch.uint8, device=dev())
+        case(f"one long segment among S={S}")
+        took = []
+        for _ in range(9):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            desc.desc_scan_segmented_i32(x, ot, y, ws=ws)
+            b.record()
+            b.synchronize()
+            took.append(a.elapsed_time(b))
+        times.append(sorted(took)[len(took) // 2])
+        assert int(y[n - 3 * (S - 1) - 1]) == n - 3 * (S - 1)
+    assert times[1] < 5 * times[0], times
