@@ -923,13 +923,21 @@ bool short_scan(int64_t n, int64_t S) { return S >= kShortCount && n <= kShortSc
 //           of 74K (a wave's unit each): 430 / 410 / 463
 //   scan    16384 of 8.7K: 226 / 231 / 319; 8192 of 23K: 301 / 288 / 299;
 //           1000 of 78K: 148 / 131 / 125; 4096 of 76K: 553 / 475 / 450
+// Up to 384 units of 8K in all (1.5 a CU) the scan takes those whatever the
+// mean, or it leaves CUs idle: one segment of 262144 7.5 / 8.4 / 9.3, two of 1.5 M
+// 11.2 / 11.5 / 12.0, 30 of 100K 10.6 / 11.3 / 12.4; of 6 M in all 18.7 / 17.5 / 16.4 as
+// one segment, 14.2 / 14.9 / 14.7 as 30.  Not the reduce, where the block that
+// ends a segment adds up the tails of all before it: one segment of 262144
+// 16.7 / 10.8 / 8.4, of 4 M 211 / 105 / 57.
 constexpr int64_t kUnit8Reduce = 32768, kUnit8Scan = 12288, kUnit16Scan = 49152;
+constexpr int64_t kFewUnitsScan = 384 * 8192;
 int reduce_by_mean(int64_t n, int64_t S, bool persistent) {
   if (n <= kUnit8Reduce * S) return 0;
   return short_reduce(n, S, persistent) ? 1 : 2;
 }
 int scan_by_mean(int64_t n, int64_t S) {
-  return n <= kUnit8Scan * S ? 0 : n <= kUnit16Scan * S ? 1 : 2;
+  if (n <= kUnit8Scan * S || n <= kFewUnitsScan) return 0;
+  return n <= kUnit16Scan * S ? 1 : 2;
 }
 
 template <class C>

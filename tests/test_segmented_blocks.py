@@ -141,3 +141,22 @@ def test_one_long_segment_does_not_chain_the_blocks():
         times.append(sorted(took)[len(took) // 2])
         assert int(y[n - 3 * (S - 1) - 1]) == n - 3 * (S - 1)
     assert times[1] < 5 * times[0], times
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("n", [384 * 8192, 384 * 8192 + 1])
+def test_few_long_segments(n):
+    """Both sides of the total at which a few long segments change their unit."""
+    S = 3
+    lengths = np.array([n // 3 - 7, n // 3 + 9, n - 2 * (n // 3) - 2], np.int64)
+    off = workloads.offsets_from_lengths(lengths)
+    x = workloads.int_uniform(n, seed=73)
+    case(f"few long segments n={n}")
+    xt, ot = to_dev(x, 1), to_dev(off)
+    y = torch.full((n,), -5, dtype=torch.int32, device=dev())
+    r = torch.full((S,), 5, dtype=torch.int64, device=dev())
+    desc.desc_scan_segmented_i32(xt, ot, y)
+    desc.desc_reduce_segmented_i32(xt, ot, r)
+    assert np.array_equal(y.cpu().numpy(), oracle.scan_segmented_i32(x, off))
+    assert np.array_equal(r.cpu().numpy(), oracle.reduce_segmented_i32(x, off))
