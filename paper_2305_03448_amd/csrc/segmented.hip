@@ -154,10 +154,13 @@ struct UnitInfo {
   bool single;                // the segment has one unit only
 };
 
-// Unit u of this block (layout::seg_unit, found by wave 0 and shared).  The
-// 64-way search takes two or three rounds of parallel loads where one
-// thread's binary search took a dependent load per step, 14 of them (8 us a
-// block) at 16384 segments.
+// Unit u of this block, found by wave 0 and shared.  The 64-way search takes
+// two or three rounds of parallel loads where a binary search takes a dependent
+// load per step, 14 of them (8 us a block) at 16384 segments.  Up to 64 segments
+// the binary search is the faster one: its position is uniform, so its loads
+// are scalar ones that hit the scalar cache (reduce of 64 rows of 4 M 181
+// against 184 us, scan 416 / 422; 1000 rows of 60000 60 against 56).
+constexpr int64_t kScalarSearch = 64;
 template <class C>
 __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t* unit_start,
                                           int64_t n, int64_t S, int64_t total, UnitInfo* out) {
@@ -166,9 +169,11 @@ __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t*
   const idx_t u = block_x().index();
   if (u >= total) return false;
   if (thread.index() < kWave) {
+    const auto us = array(unit_start, S + 1);
+    const idx_t seg = S <= kScalarSearch ? layout::seg_of_unit(us, S, u)
+                                         : wave_owner(unit_start, S, u);
     const layout::SegUnit su =
-        layout::seg_unit_of(array(offsets, S + 1), array(unit_start, S + 1), n, C::unit, u,
-                            wave_owner(unit_start, S, u));
+        layout::seg_unit_of(array(offsets, S + 1), us, n, C::unit, u, seg);
     if (thread.index() == 0) {
       s_info[0] = su.seg; s_info[1] = su.j; s_info[2] = su.begin;
       s_info[3] = su.len; s_info[4] = su.single;

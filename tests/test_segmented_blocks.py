@@ -160,3 +160,25 @@ def test_few_long_segments(n):
     desc.desc_reduce_segmented_i32(xt, ot, r)
     assert np.array_equal(y.cpu().numpy(), oracle.scan_segmented_i32(x, off))
     assert np.array_equal(r.cpu().numpy(), oracle.reduce_segmented_i32(x, off))
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("S", [63, 64, 65, 129])
+def test_both_searches_of_a_units_segment(S):
+    """Both sides of the segment count at which the search changes, with empty
+    segments at the ends and between, and segments of several units."""
+    g = workloads.rng(79)
+    lengths = g.integers(0, 40_000, S)
+    lengths[[0, 1, S // 2, S // 2 + 1, S - 1]] = 0
+    off = workloads.offsets_from_lengths(np.asarray(lengths, np.int64))
+    x = workloads.int_uniform(int(off[-1]), seed=83)
+    case(f"segment searches S={S}")
+    xt, ot = to_dev(x), to_dev(off)
+    y = torch.full((x.size,), -5, dtype=torch.int32, device=dev())
+    desc.desc_scan_segmented_i32(xt, ot, y)
+    assert np.array_equal(y.cpu().numpy(), oracle.scan_segmented_i32(x, off))
+    rows = workloads.int_uniform(S * 9001, seed=89).reshape(S, 9001)
+    r = torch.full((S,), 5, dtype=torch.int64, device=dev())
+    desc.desc_reduce_batched_i32(to_dev(rows), r)
+    assert np.array_equal(r.cpu().numpy(), rows.astype(np.int64).sum(1))
