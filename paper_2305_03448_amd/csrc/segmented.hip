@@ -909,16 +909,23 @@ bool persistent_fits(int64_t n, int64_t S) {
 //     and below 2000 segments within 1 us either way; of 74K, where the
 //     persistent reduce is as fast (8192: 371 / 367) and a block per unit is
 //     not (9000: 435 / 410);
-//   scan, mean length     380: 4000 segments 18 / 16, 8192: 31 / 24, 16384: 57 / 38
-//                        1080: 16384 segments 61 / 48
-//                        2900: 4000 segments 27 / 37, 16384: 99 / 112, since the
-//     units of a long segment in one block follow each other where separate
-//     blocks overlap them, and 10 / 14 already at 1024 segments of 380.
-constexpr int64_t kShortCount = 2048, kShortReduceMean = 32768, kShortScanMean = 1536;
+//   scan, mean length     380: 2048 segments 11.8 / 14.4, 4096: 17.6 / 15.9, 8192: 30 / 24
+//                        1000: 2048 segments 13 / 17, 4096: 19 / 20, 6000: 27 / 25, 8192: 33 / 29
+//                        1370: 2048 segments 15 / 18, 4096: 21 / 22, 6000: 28.0 / 28.1,
+//                              8192: 35 / 34, 16384: 61 / 55
+//                        2900: 4000 segments 27 / 37, 16384: 99 / 112
+//     since the units of long segments in one block follow each other where
+//     separate blocks overlap them.  Lengths all alike above 1024, the longest
+//     segment of a wave, are its worst case (1030: 2048 segments 12 / 17, 6000
+//     26 / 28, 16384 57 / 57), and its best below (2048 of 500: 9).
+constexpr int64_t kShortCount = 2048, kShortReduceMean = 32768;
+constexpr int64_t kManyShort = 6000, kShortScanMean = 1024, kManyShortScanMean = 1536;
 bool short_reduce(int64_t n, int64_t S, bool persistent) {
   return S >= kShortCount && (n <= kShortReduceMean * S || !persistent);
 }
-bool short_scan(int64_t n, int64_t S) { return S >= kShortCount && n <= kShortScanMean * S; }
+bool short_scan(int64_t n, int64_t S) {
+  return S >= kShortCount && n <= (S < kManyShort ? kShortScanMean : kManyShortScanMean) * S;
+}
 
 // Unit size by mean length ("by_mean"; us, units of 8K / 16K / 32K): a unit
 // shorter than the segments splits them into more units to look back over,

@@ -182,3 +182,19 @@ def test_both_searches_of_a_units_segment(S):
     r = torch.full((S,), 5, dtype=torch.int64, device=dev())
     desc.desc_reduce_batched_i32(to_dev(rows), r)
     assert np.array_equal(r.cpu().numpy(), rows.astype(np.int64).sum(1))
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("S,mean", [(2048, 1024), (2048, 1025), (5999, 1025), (6000, 1025),
+                                    (6000, 1536), (6000, 1537)])
+def test_mean_lengths_where_the_scan_changes_form(S, mean):
+    g = workloads.rng(97)
+    lengths = np.minimum(g.integers(0, 2 * mean, S), g.integers(0, 9000, S))
+    lengths[3] += mean * S - int(lengths.sum())          # one takes up the rest
+    off = workloads.offsets_from_lengths(np.asarray(lengths, np.int64))
+    x = workloads.int_uniform(int(off[-1]), seed=101)
+    case(f"scan of S={S} segments of {mean} on average")
+    y = torch.full((x.size,), -5, dtype=torch.int32, device=dev())
+    desc.desc_scan_segmented_i32(to_dev(x, 1), to_dev(off), y)
+    assert np.array_equal(y.cpu().numpy(), oracle.scan_segmented_i32(x, off))
