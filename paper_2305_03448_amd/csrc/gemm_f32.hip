@@ -133,6 +133,29 @@ constexpr DirectForm kDirect[] = {
 };
 constexpr int kDirectForms = (int)(sizeof(kDirect) / sizeof(kDirect[0]));
 
+// Short K over many tiles is bound by C and by the ends of the tiles, which
+// three LDS-staged 64 x 64 blocks a CU overlap and the direct forms, alone on
+// a CU or two to it, do not: 102400 x 64 x 32 11.9 us against 18.4, 204800 x 32 x 16
+// 14.7 / 19.5, 20000 x 256 x 64 13.3 / 15.4, 3200 x 512 x 16 4.8 / 5.6.  The
+// staged form's time by tiles of 64 x 64 (t) and K: 400 tiles 4.8 us at K = 16 and
+// 7.1 at 64, 3200 tiles 14.4 and 26; direct forms take 2.5 us more than
+// their estimate, which counts rounds alone, up to one residency of the staged
+// form (768 tiles) and 2 beyond.  Not where the direct form runs one round of
+// tiles that the other would need two for (25600 x 100 x 16 5.6 / 7.1), not for
+// narrow C, of which a 64-wide tile wastes most (102400 x 16 x 64 9.7 / 15.8), and on
+// operands that are not in 16-byte groups, which the staged form reads word by
+// word, only up to K = 16 (204800 x 30: K = 16 15.3 / 19.7, 32 22.0 / 23.5, 64 35.7 / 26.0).
+bool short_k_staged(const GemmProblemF32& g, const DirectForm& d, double direct_us) {
+  const int64_t t = ((g.M + 63) / 64) * ((g.N + 63) / 64);
+  const int64_t direct_tiles = ((g.M + d.bm - 1) / d.bm) * ((g.N + d.bn - 1) / d.bn);
+  const bool vec = gemm_f32::vec_ok(g.A, g.lda, g.B, g.ldb);
+  if (g.N < 24 || g.K > (!vec ? 16 : g.N < 48 ? 32 : 64) || g.M * g.N * g.K >= (int64_t)1 << 30)
+    return false;
+  if (t <= 256 || (t > 768 && direct_tiles <= 256)) return false;
+  const double r = (double)t / 256, first = r < 3 ? r : 3.0, k = (double)g.K * 1e-3;
+  return 3.3 + 12.2 * k * first + r * (0.7 + 14.9 * k) < direct_us + (t <= 768 ? 2.5 : 2.0);
+}
+
 // "_rm": the row-major-A tile form; "_w8": eight waves (2 x 4).  "by_shape":
 // a direct form or the LDS-staged 128 x 128 tile, whichever the call's M, N
 // and K make faster; "dBMxBN": that direct form (by_shape where a row of C is
@@ -182,7 +205,9 @@ hipError_t gemm_f32(const float* A, int64_t lda, const float* B, int64_t ldb, fl
       const double ns = 58.0 + 9.0 / (tiles <= 256 ? 1.0 : tiles / 256);
       const bool staged_ok = gemm_f32::clamped_tile<Staged>(g);
       if (d && (!staged_ok || us <= rounds_us(M, N, K, 128, 128, ns, K < 512 ? 4.0 : 2.0)))
-        return d->launch(g, s);
+        return short_k_staged(g, *d, us)
+                   ? launch_gemm<GemmCfgF32<64, 64, 16>>(A, lda, B, ldb, Cm, ldc, M, N, K, s)
+                   : d->launch(g, s);
     }
     // whole tiles of aligned rows keep the form without clamps (4096^3: 941
     // against 956 us)

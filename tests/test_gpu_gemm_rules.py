@@ -1,0 +1,41 @@
+"""FP32 products on both sides of the lines that choose a form by M, N and K,
+against exact integer products: operands that are and are not in 16-byte
+groups, NaN beside every row, and guard words around C."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_03448_amd as desc
+import workloads
+from gpu_util import case, needs_gpu
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+
+def _check(M, N, K, pad):
+    case(f"gemm f32 {M}x{N}x{K} pad {pad}")
+    g = workloads.rng(91)
+    A = g.integers(-4, 5, size=(M, K)).astype(np.float32)
+    B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
+
+    def padded(x):
+        t = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), device="cuda")
+        t[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+        return t[:, :x.shape[1]]
+    buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
+    desc.desc_gemm(padded(A), padded(B), buf[:M, :N])
+    want = (A.astype(np.float64) @ B.astype(np.float64)).astype(np.float32)
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[:M, :N], want)
+    assert (got[M:] == -7).all() and (got[:, N:] == -7).all(), "wrote outside C"
+
+
+@pytest.mark.parametrize("pad", [0, 1, 4])
+@pytest.mark.parametrize("M,N,K", [
+    (16384, 64, 32), (16385, 64, 32),            # 256 tiles of 64 x 64, 257
+    (3201, 500, 64), (3200, 512, 65),            # K limit of operands in groups
+    (20000, 30, 16), (20000, 30, 17),            # and of the others
+    (30000, 47, 32), (30000, 47, 33), (30000, 23, 16), (30000, 24, 16),
+    (24576, 100, 16), (49153, 64, 16)])          # one residency, and past it
+def test_short_k(M, N, K, pad):
+    _check(M, N, K, pad)
