@@ -54,8 +54,10 @@ void gemm_f32w_kernel(
 }
 
 // The clamped form (gemm_f32.hpp): tiles inside C, and the ones at its edges.
-template <class C>
-__global__ __launch_bounds__(C::threads) __attribute__((amdgpu_waves_per_eu(C::depth)))
+// It takes 131 registers, three blocks a CU; kBlocks = 4 holds it to 128, at the
+// cost of a few spilled words.
+template <class C, int kBlocks>
+__global__ __launch_bounds__(C::threads) __attribute__((amdgpu_waves_per_eu(kBlocks)))
 void gemm_f32c_kernel(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
     float* __restrict__ Cm, int64_t ldc, int64_t M, int64_t N, int64_t K) {
@@ -84,13 +86,22 @@ hipError_t launch_gemm_w(const float* A, int64_t lda, const float* B, int64_t ld
 }
 
 // The clamped form where the call's spans allow it, else the guarded one.
+// 769 to 1024 tiles are one residency of four blocks a CU and leave three a
+// nearly empty last round: 4000 x 4000 at K = 512 156 us in three (140 in the
+// guarded form), 129 in four; 2796 x 5424 x 1012 294 and 247; about even where the
+// rounds happen to fit (2496 x 5760 x 896 218 / 216); 3 % the other way below
+// K = 100 (6272 x 2368 x 96 32.7 / 33.7), and up to 18 % past 1024 tiles.
 template <class C>
 hipError_t launch_gemm_c(const GemmProblemF32& g, hipStream_t s) {
   if (!gemm_f32::clamped_tile<C>(g))
     return launch_gemm_w<C>(g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K, s);
   const int64_t tiles = ((g.M + C::bm - 1) / C::bm) * ((g.N + C::bn - 1) / C::bn);
-  hipLaunchKernelGGL(gemm_f32c_kernel<C>, dim3((unsigned)tiles), dim3(C::threads), 0, s, g.A,
-                     g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K);
+  if (tiles > 3 * 256 && tiles <= 4 * 256 && g.K >= 128)
+    hipLaunchKernelGGL((gemm_f32c_kernel<C, 4>), dim3((unsigned)tiles), dim3(C::threads), 0, s,
+                       g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K);
+  else
+    hipLaunchKernelGGL((gemm_f32c_kernel<C, C::depth>), dim3((unsigned)tiles), dim3(C::threads), 0,
+                       s, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.M, g.N, g.K);
   return hipGetLastError();
 }
 

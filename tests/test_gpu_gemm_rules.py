@@ -39,3 +39,12 @@ def _check(M, N, K, pad):
     (24576, 100, 16), (49153, 64, 16)])          # one residency, and past it
 def test_short_k(M, N, K, pad):
     _check(M, N, K, pad)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (3071, 4097, 128), (3073, 3969, 128),         # 792 and 800 tiles of 128 x 128
+    (4000, 4000, 127), (4000, 4000, 131),         # 1024, both sides of its least K
+    (4097, 3969, 128)])                           # 1056
+def test_one_residency_of_clamped_tiles(M, N, K):
+    _check(M, N, K, 1)
+    _check(M, N, K, 0)
