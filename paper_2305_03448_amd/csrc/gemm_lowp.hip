@@ -1134,6 +1134,10 @@ hipError_t gemm_bf16x3(const float* A, int64_t lda, const float* B, int64_t ldb,
         return kDirect[cfg - kByShape - 1].launch(g, s);
       double us = 0;
       const DirectForm* d = best_direct(kDirect, kDirectForms, M, N, K, false, &us);
+      // below one stage of K (32) the direct form reads word by word, the fused
+      // one in 16-byte groups where A's rows are whole ones: 768000 x 32 x 16 57 us
+      // against 70, 3200 x 512 x 24 5.8 / 7.1 (of K = 12 even, 25600 x 64 6.9 / 6.4)
+      if (K >= 16 && K < 32 && K % 4 == 0 && gemm_f32::vec_ok(A, lda, A, lda)) us = 1.25 * us + 0.3;
       if (d && us <= fused && us <= dma) return d->launch(g, s);
     }
     cfg = dma < fused ? kBf16Dma : fused256_us(M, N, K) < fused128_us(M, N, K) ? 6 : 5;

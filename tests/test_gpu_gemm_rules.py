@@ -1,4 +1,4 @@
-"""FP32 products on both sides of the lines that choose a form by M, N and K,
+"""Products on both sides of the lines that choose a form by M, N and K,
 against exact integer products: operands that are and are not in 16-byte
 groups, NaN beside every row, and guard words around C."""
 import numpy as np
@@ -12,8 +12,8 @@ from gpu_util import case, needs_gpu
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
 
-def _check(M, N, K, pad):
-    case(f"gemm f32 {M}x{N}x{K} pad {pad}")
+def _check(M, N, K, pad, mode="f32"):
+    case(f"gemm {mode} {M}x{N}x{K} pad {pad}")
     g = workloads.rng(91)
     A = g.integers(-4, 5, size=(M, K)).astype(np.float32)
     B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
@@ -23,7 +23,7 @@ def _check(M, N, K, pad):
         t[:, :x.shape[1]] = torch.from_numpy(x).cuda()
         return t[:, :x.shape[1]]
     buf = torch.full((M + 1, N + pad), -7.0, device="cuda")
-    desc.desc_gemm(padded(A), padded(B), buf[:M, :N])
+    desc.desc_gemm(padded(A), padded(B), buf[:M, :N], mode=mode)
     want = (A.astype(np.float64) @ B.astype(np.float64)).astype(np.float32)
     got = buf.cpu().numpy()
     assert np.array_equal(got[:M, :N], want)
@@ -48,3 +48,11 @@ def test_short_k(M, N, K, pad):
 def test_one_residency_of_clamped_tiles(M, N, K):
     _check(M, N, K, 1)
     _check(M, N, K, 0)
+
+
+@pytest.mark.parametrize("pad", [0, 1, 4])
+@pytest.mark.parametrize("M,N,K", [(3200, 512, 15), (3200, 512, 16), (3200, 512, 28), (3201, 509, 28),
+                                   (3200, 512, 31), (3200, 512, 32), (50000, 31, 20)])
+def test_split_below_one_stage(M, N, K, pad):
+    # small integers are bfloat16 values: exact products
+    _check(M, N, K, pad, "bf16x3")
