@@ -1045,10 +1045,13 @@ using Fp8D32 = DirectNtCfg<1, 1, 16, 2>;
 using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;
 
 // The FP8 form of a call.  With up to 256 tiles of 32 x 32 (one a CU) and K in
-// the registers of one block, or 512 tiles and half that K, the one-launch
-// form saves two launches (512^3 10.0 against 17.4 us, 700 x 700 x 300 16.5
-// against 20.9; beyond, its repeated operand reads cost more than they: 1024 x
-// 1024 x 512 32 against 17).  With up to 256 tiles of 32 x 32, then of 64 x 64,
+// the registers of one block, the one-launch form saves two launches (64^3 8.2
+// us against 10.3 in the staged tiles, 16 x 8000 x 512 8.2 / 13.2); up to 512 tiles
+// only where one operand has a single tile of rows, so that the other is read
+// once, and K is long enough to pay for its words (16 x 16000: K = 256 13.2 / 12.0
+// in 64 x 64 direct tiles, 512 14.4 / 15.9, 1024 20.9 / 24.3; but 128 x 4096 x 64 16.3 /
+// 9.7, 700 x 700 x 300 16.5 / 10.5, where every tile reads both operands again).
+// With up to 256 tiles of 32 x 32, then of 64 x 64,
 // the direct tiles share K among 16 or 8 waves (64 x 64 x 4096 22 against 36
 // us, 128 x 2048 x 2048 20.5 against 27, 1024 x 1024 x 4096 34 against 37).
 // Beyond that the LDS-staged tiles: 128 x 128 or the direct-to-LDS 256 x 256
@@ -1056,7 +1059,8 @@ using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;
 int fp8_by_shape(int64_t M, int64_t N, int64_t K, int cls) {
   auto tiles = [&](int64_t t) { return (double)((M + t - 1) / t) * (double)((N + t - 1) / t); };
   constexpr int64_t kOnce = gemm_fp8::kFusedWaves * gemm_fp8::kFusedStep;
-  if ((tiles(32) <= 256 && K <= kOnce) || (tiles(32) <= 512 && K <= kOnce / 2)) return kFp8Fused;
+  if (tiles(32) <= 256 && K <= kOnce) return kFp8Fused;
+  if (tiles(32) <= 512 && std::min(M, N) <= 32 && K > kOnce / 4 && K <= kOnce) return kFp8Fused;
   if (tiles(32) <= 256) return kFp8Fused + 1;
   if (tiles(64) <= 256) return kFp8D64;
   if (cls < 2) return cls == 0 ? 1 : 0;

@@ -56,3 +56,24 @@ def test_one_residency_of_clamped_tiles(M, N, K):
 def test_split_below_one_stage(M, N, K, pad):
     # small integers are bfloat16 values: exact products
     _check(M, N, K, pad, "bf16x3")
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (512, 512, 64), (545, 512, 64),               # 256 tiles of 32 x 32, 288
+    (1024, 512, 512), (512, 1025, 512),           # 512, 528
+    (32, 16384, 256), (32, 16384, 257), (33, 8192, 257), (16000, 17, 1024), (16000, 17, 1025),
+    (1024, 1024, 64), (1025, 1024, 64)])          # 256 tiles of 64 x 64, 272
+def test_fp8_forms_of_few_tiles(M, N, K):
+    # e4m3 values 448 / 2^i with 448 in every row and column: unit scales, and
+    # products and sums that are exact in the instruction and in FP32
+    case(f"gemm fp8 {M}x{N}x{K}")
+    g = workloads.rng(95)
+    A, B = (np.float32(448) * (g.integers(-1, 2, size=s) / 2.0 ** g.integers(0, 3, size=s))
+            .astype(np.float32) for s in ((M, K), (K, N)))
+    A[:, K // 2] = 448
+    B[K // 2, :] = 448
+    buf = torch.full((M + 1, N), -7.0, device="cuda")
+    desc.desc_gemm(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), buf[:M], mode="fp8")
+    want = (torch.from_numpy(A).cuda().double() @ torch.from_numpy(B).cuda().double()).float()
+    assert torch.equal(buf[:M], want)
+    assert bool((buf[M] == -7).all()), "wrote outside C"
