@@ -624,14 +624,18 @@ __global__ __launch_bounds__(kBlock) void quant_cols_t_kernel(const float* __res
 
 // Which encode: the LDS tiles up to 8192 of them, since they make four times
 // the blocks (3072 x 512 6.1 us against 7.9, 2560 x 3072 12.3 / 15.7, 4096 x
-// 4096 18.5 both); up to 2048 where their loads are single ones (B not aligned
-// to 16 bytes: 2110 x 1593 2 us ahead of the other's 280 blocks).
+// 4096 18.5 both); up to 2048 where their loads are single ones, B starting off a
+// 16-byte boundary.  Rows that each start at another offset from one cost the
+// 16-byte loads more than single ones (an FP8 product of 300 rows with 6295
+// columns at K = 4916 149 us in LDS tiles, 160 without; 12001 at K = 4099 220 and
+// 263), up to about K = 6000 (5001 columns at K = 8000 187 and 174).
 template <bool kNt>
 hipError_t launch_cols_t(const float* B, int64_t K, int64_t N, int64_t ldb, const float* part,
                          int64_t nslices, int64_t ldp, uint8_t* qt, int64_t n_out, int64_t k_out,
                          int64_t ldq, float* scale, bool vec_in, bool vec_out, hipStream_t s) {
   const int64_t tk = (k_out + 63) / 64, tn = (n_out + 63) / 64;
-  if (tk * tn <= 2048 || (tk * tn <= 8192 && vec_in)) {
+  const bool odd_rows = ldb % 4 != 0 && k_out <= 6144 && tn <= 65535;
+  if (tk * tn <= 2048 || (tk * tn <= 8192 && vec_in) || odd_rows) {
     hipLaunchKernelGGL(quant_cols_tile_kernel, dim3((unsigned)tk, (unsigned)tn), dim3(kBlock), 0, s,
                        B, K, N, ldb, part, nslices, ldp, qt, n_out, k_out, ldq, scale, vec_in,
                        vec_out);
