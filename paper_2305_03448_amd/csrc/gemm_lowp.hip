@@ -1208,10 +1208,16 @@ hipError_t gemm_fp8(const float* A, int64_t lda, const float* B, int64_t ldb, fl
     return launch_fp8_once<decltype(cfg_tag)>(A, M, lda, qa, L.Mp, sa, B, N, ldb, qb, L.Np, sb, K,
                                               L.Kp, s);
   };
+  // One launch, unless B is wide against A and K short: a strip's block covers
+  // 512 values of K, and with a quarter of it in use the two launches are ahead
+  // (16 rows, K = 16: 65000 columns 23.9 us against 28.5, 400000 88 / 138, but 30000
+  // 15.7 / 16.6; K = 100: 100000 columns 41.4 / 44.3, 65000 30.9 / 29.3, 100000 of 2000
+  // rows 211 / 208), and of rows it makes fewer blocks (8192 x 8192 x 16 66 / 55).
+  const bool wide_b = K <= 32 ? N > 40000 && N >= 16 * M : K <= 128 && N > 81920 && N >= 64 * M;
   // the product runs only over codes that were written: a pre-pass that is not
   // launched (2^26 rows; 2^24 beyond K = 2048, a block a row) ends the call
   hipError_t pre;
-  if (K > 0 && L.Kp <= 2048) {
+  if (K > 0 && L.Kp <= 2048 && !wide_b) {
     pre = L.Kp <= 512    ? once(OnceCfg<4>{})
           : L.Kp <= 1024 ? once(OnceCfg<8>{})
                          : once(OnceCfg<16>{});

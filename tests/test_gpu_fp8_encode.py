@@ -38,3 +38,30 @@ def test_column_codes(K, N, offset):
     assert torch.equal(s[:N].view(torch.int32), want_s.view(torch.int32))
     assert bool((q[:offset] == 0x55).all()) and bool((q[offset + N * K:] == 0x55).all())
     assert float(s[N]) == -7.0
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 40000, 32), (16, 40001, 32), (2501, 40016, 32),
+                                   (16, 81920, 33), (15, 81921, 33), (15, 81921, 128), (16, 81924, 129),
+                                   (1300, 83200, 100), (1301, 83200, 100)])
+def test_pre_pass_of_wide_operands(M, N, K):
+    """Both sides of the lines between the pre-pass of one launch and of two: the
+    codes that the product leaves in its workspace."""
+    case(f"gemm fp8 {M}x{N}x{K}")
+    g = torch.Generator(device=dev()).manual_seed(99)
+    A, B = torch.randn(M, K, device=dev(), generator=g), torch.randn(K, N, device=dev(), generator=g)
+    C = torch.empty(M, N, device=dev())
+    ws = torch.full((desc.desc_gemm_workspace("fp8", M, N, K),), 0x5A, dtype=torch.uint8,
+                    device=dev())
+    desc.desc_gemm(A, B, C, mode="fp8", ws=ws)
+    up = lambda x, m: -(-x // m) * m
+    rows, kp = (up(M, 256), up(N, 256)), up(K, 128)
+    scales = up(rows[0] * kp, 256) + up(rows[1] * kp, 256)
+    for at, r, X, scale in ((0, rows[0], A, scales),
+                            (up(rows[0] * kp, 256), rows[1], B.t(), scales + up(4 * rows[0], 256))):
+        q = torch.empty(X.shape, dtype=torch.uint8, device=dev())
+        want = torch.empty(X.shape[0], device=dev())
+        desc.desc_quant_e4m3_rows(X.contiguous(), q, want)
+        got = ws[at:at + r * kp].view(r, kp)
+        assert torch.equal(got[:X.shape[0], :K], q)
+        assert not bool(got[X.shape[0]:].any()) and not bool(got[:, K:].any())
+        assert torch.equal(ws[scale:scale + 4 * X.shape[0]].view(torch.float32), want)
