@@ -293,14 +293,13 @@ __global__ __launch_bounds__(kBlock) void grouped_plan_mixed_kernel(const desc_g
     const idx_t i = base + thread.index();
     MixPlan m{0, 0, 0, 0, 0, 0};
     if (i < G) m = mix_plan(as_f32(pr[ord[i]]), use_big);
-    int64_t e_small;
-    const int64_t t_big = block_excl(m.bigs, &ex, lds);
-    const int64_t t_small = block_excl(m.smalls, &e_small, lds);
-    if (i < G) {
-      array(w.big_start, G)[i] = (int32_t)(c_big + ex);
-      array(w.small_start, G + 1)[i] = c_small + e_small;
+    if (use_big) {                   // without large tiles nothing reads their prefix
+      const int64_t t_big = block_excl(m.bigs, &ex, lds);
+      if (i < G) array(w.big_start, G)[i] = (int32_t)(c_big + ex);
+      c_big += t_big;
     }
-    c_big += t_big;
+    const int64_t t_small = block_excl(m.smalls, &ex, lds);
+    if (i < G) array(w.small_start, G + 1)[i] = c_small + ex;
     c_small += t_small;
   }
   if (thread.index() == 0) {
@@ -341,7 +340,7 @@ void grouped_mixed_kernel(const desc_gemm_problem* probs, int64_t G, MixWs w) {
   auto thread = thread_x<kBlock>();
   const int64_t TS = w.total[0], TB = w.total[1];
   const bool in_lds = G <= kMixLdsProblems;
-  if (in_lds) {
+  if (in_lds && TB > 0) {
     for (idx_t i = thread.index(); i <= G; i += kBlock)
       s_start[i] = i < G ? array(w.big_start, G)[i] : TB;
     sync(thread);
