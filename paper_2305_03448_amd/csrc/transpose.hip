@@ -137,13 +137,21 @@ bool any_shape(const void* in, const void* out, int64_t rows, int64_t cols, int 
 template <class E>
 hipError_t transpose_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
                          hipStream_t s);
+template <class E, int kT, int kThreads, bool kNt>
+hipError_t launch_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
+                      hipStream_t s);
 
-template <class C>
+// kByShape: matrices that are not whole tiles take the tile that transpose_any
+// picks, else C's.
+template <class C, bool kByShape = false>
 hipError_t launch_transpose(const uint32_t* in, uint32_t* out, int64_t batch, int64_t rows,
                             int64_t cols, hipStream_t s) {
   constexpr int T = C::t;
-  if (any_shape<uint32_t>(in, out, rows, cols, T))
-    return transpose_any<uint32_t>(in, out, batch, rows, cols, s);
+  if (any_shape<uint32_t>(in, out, rows, cols, T) &&
+      launch::grid_fits((cols + T - 1) / T, C::block)) {
+    if constexpr (kByShape) return transpose_any<uint32_t>(in, out, batch, rows, cols, s);
+    else return launch_any<uint32_t, T, C::block, C::nt>(in, out, batch, rows, cols, s);
+  }
   // past 2^29 columns (2^30 of a 128-wide tile of 512 threads) 128 x 128 tiles
   // of 256 threads, whose grid takes every column count the call accepts
   using Wide = TransposeCfg<128, C::nt>;
@@ -354,6 +362,7 @@ bool any_shape(const void* in, const void* out, int64_t rows, int64_t cols, int 
 template <class E, int kT, int kThreads, bool kNt>
 hipError_t launch_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
                       hipStream_t s) {
+  if (!launch::grid_fits((cols + kT - 1) / kT, kThreads)) return hipErrorInvalidConfiguration;
   using C = AnyShape<E, kT, kNt, kThreads>;
   const dim3 grid((unsigned)((cols + kT - 1) / kT), (unsigned)((rows + kT - 1) / kT),
                   (unsigned)batch);
@@ -414,11 +423,14 @@ hipError_t launch_transpose_elem(const void* in, void* out, int64_t batch, int64
   return hipGetLastError();
 }
 
+// "tT": tiles of T x T words whatever the matrix; "by_shape": the tile by size,
+// of whole aligned tiles and of the others each by its own measurements.
 constexpr const char* kNames[] = {"t64_nt", "t64", "t32_nt", "t32", "t128_nt", "t128",
-                                   "t128_nt_b512", "t128_b512"};
-constexpr int kDefaults[tune::kClasses] = {0, 0, 0, 0};
+                                   "t128_nt_b512", "t128_b512", "by_shape"};
+constexpr int kByShape = 8;
+constexpr int kDefaults[tune::kClasses] = {kByShape, kByShape, kByShape, kByShape};
 const bool kRegistered =
-    (tune::register_op(tune::kTranspose32, "transpose_32", 8, kNames, kDefaults), true);
+    (tune::register_op(tune::kTranspose32, "transpose_32", 9, kNames, kDefaults), true);
 
 }  // namespace
 
@@ -433,7 +445,15 @@ hipError_t transpose_32(const uint32_t* in, uint32_t* out, int64_t batch, int64_
   if (batch == 0 || rows == 0 || cols == 0) return hipSuccess;
   (void)kRegistered;
   const int64_t size = batch * rows * cols;
-  switch (tune::get(tune::kTranspose32, tune::size_class(tune::kTranspose32, size))) {
+  const int cls = tune::size_class(tune::kTranspose32, size);
+  const int cfg = tune::get(tune::kTranspose32, cls);
+  if (cfg == kByShape) {
+    if (cls < 2) return launch_transpose<TransposeCfg<32, false>, true>(in, out, batch, rows, cols, s);
+    if (cls < 3)
+      return launch_transpose<TransposeCfg512<128, false>, true>(in, out, batch, rows, cols, s);
+    return launch_transpose<TransposeCfg512<128, true>, true>(in, out, batch, rows, cols, s);
+  }
+  switch (cfg) {
     case 1: return launch_transpose<TransposeCfg<64, false>>(in, out, batch, rows, cols, s);
     case 2: return launch_transpose<TransposeCfg<32, true>>(in, out, batch, rows, cols, s);
     case 3: return launch_transpose<TransposeCfg<32, false>>(in, out, batch, rows, cols, s);
