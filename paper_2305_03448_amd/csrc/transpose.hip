@@ -372,14 +372,19 @@ hipError_t launch_any(const void* in, void* out, int64_t batch, int64_t rows, in
 }
 
 // Tile by size: the largest tile writes the longest pieces of output rows and
-// wins once it fills the GPU; below about 2^20 bytes (2^23 words of 4 bytes)
-// smaller tiles finish sooner (100 x 200 16-bit elements 3.2 against 4.0 us,
-// 500 x 600 words 4.0 against 5.0).  Streaming accesses only where both
-// arrays together outgrow the last-level cache (8192 x 6144 words, 403 MB: 71
-// us against 78; 4112^2 doubles, 271 MB: 70 against 46) and every piece of an
-// output row is whole 128-byte lines: two blocks share a line otherwise, and
-// it must stay in the cache to be written once (16383 x 16381 bytes: 225 us
-// against 197).
+// wins once it fills the GPU; below, smaller tiles finish sooner.  us in tiles of
+// 64 and 128, for one matrix and for a batch of 12 (ragged, near-square):
+//   bytes   1.1 MB 2.8 / 3.6 and 3.0 / 3.7, 4 MB 4.5 / 4.4 and 4.8 / 5.5, 8 MB 7.3 /
+//           7.0 and 7.2 / 7.8, 16 MB 14.6 / 11.0 and 14.9 / 11.8
+//   16 bits 1.1 MB 3.0 / 4.1 and 3.0 / 4.1, 4 MB 4.1 / 4.7 and 4.3 / 4.9, 8 MB 5.7 /
+//           5.7 and 5.9 / 6.7, 16 MB 10.4 / 8.8 and 10.3 / 9.4
+//   words   8 MB 4.7 / 5.4 and 4.8 / 5.9, 16 MB 7.6 / 7.3 and 7.8 / 8.6, 32 MB 13.9 /
+//           12.7 and 14.1 / 13.8; 0.25 MB 2.4 in tiles of 32, 2.8 of 64
+// Streaming accesses only where both arrays together outgrow the last-level
+// cache (8192 x 6144 words, 403 MB: 71 us against 78; 4112^2 doubles, 271 MB: 70
+// against 46) and every piece of an output row is whole 128-byte lines: two
+// blocks share a line otherwise, and it must stay in the cache to be written
+// once (16383 x 16381 bytes: 225 us against 197).
 template <class E>
 hipError_t transpose_any(const void* in, void* out, int64_t batch, int64_t rows, int64_t cols,
                          hipStream_t s) {
@@ -389,15 +394,12 @@ hipError_t transpose_any(const void* in, void* out, int64_t batch, int64_t rows,
   if constexpr (sizeof(E) == 8)
     return lines ? launch_any<E, 64, 512, true>(in, out, batch, rows, cols, s)
                  : launch_any<E, 64, 512, false>(in, out, batch, rows, cols, s);
-  if constexpr (sizeof(E) == 4) {
+  if constexpr (sizeof(E) == 4)
     if (count < (int64_t)1 << 16)
       return launch_any<E, 32, 256, false>(in, out, batch, rows, cols, s);
-    if (count < (int64_t)1 << 23)
+  if constexpr (sizeof(E) <= 4)
+    if (count < (int64_t)(sizeof(E) == 4 ? 6 : 4) << 20)
       return launch_any<E, 64, 256, false>(in, out, batch, rows, cols, s);
-  } else if constexpr (sizeof(E) < 4) {
-    if (count * (int64_t)sizeof(E) < (int64_t)1 << 20)
-      return launch_any<E, 64, 256, false>(in, out, batch, rows, cols, s);
-  }
   if constexpr (sizeof(E) <= 4)
     return lines ? launch_any<E, 128, 512, true>(in, out, batch, rows, cols, s)
                  : launch_any<E, 128, 512, false>(in, out, batch, rows, cols, s);

@@ -44,6 +44,26 @@ def test_edges_of_a_configured_tile(name, t):
             desc.desc_config_set(OP, cls, -1)
 
 
+# Both sides of the sizes at which the tile changes: 2^16 words, 4 x 2^20 bytes
+# and 16-bit elements, 6 x 2^20 words.
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("elem,batch,rows,cols", [
+    (4, 1, 255, 257), (4, 1, 257, 256), (4, 5, 1121, 1121), (4, 6, 1025, 1025), (1, 1, 2047, 2049),
+    (1, 1, 2049, 2048), (2, 3, 1182, 1182), (2, 3, 1183, 1183), (1, 7, 77, 7777), (2, 7, 7777, 78)])
+def test_sizes_where_the_tile_changes(elem, batch, rows, cols):
+    case(f"transpose {elem}-byte {batch}x{rows}x{cols}")
+    dtype = {1: torch.uint8, 2: torch.int16, 4: torch.int32}[elem]
+    n = batch * rows * cols
+    x = torch.randint(0, 256, (n * elem,), dtype=torch.uint8,
+                      device="cuda").view(dtype).view(batch, rows, cols)
+    buf = torch.zeros(n + 16, dtype=dtype, device="cuda")
+    y = buf[8:8 + n].view(batch, cols, rows)
+    desc.desc_transpose_batched(x, y)
+    assert torch.equal(y, x.transpose(1, 2))
+    assert int(buf[:8].abs().sum()) == 0 and int(buf[8 + n:].abs().sum()) == 0
+
+
 # Streaming accesses, from 402 MB of both arrays in whole 128-byte output
 # lines: whole lines of rows, a column count that is no multiple of a group.
 @pytest.mark.gpu
