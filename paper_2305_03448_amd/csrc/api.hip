@@ -742,11 +742,10 @@ desc_status desc_config_load(const char* path) {
     char op[64], cfg[64];
     int cls = -1;
     if (line[0] == '#' || sscanf(line, "%63s %d %63s", op, &cls, cfg) != 3) continue;
-    int o = -1, c = -1;
+    int o = -1;
     for (int i = 0; i < desc::tune::kNumOps; ++i)
       if (desc::tune::op_name(i) && strcmp(desc::tune::op_name(i), op) == 0) o = i;
-    for (int j = 0; o >= 0 && j < desc::tune::config_count(o); ++j)
-      if (strcmp(desc::tune::config_name(o, j), cfg) == 0) c = j;
+    const int c = desc::tune::config_by_name(o, cfg);
     if (o < 0 || c < 0 || !desc::tune::set(o, cls, c)) st = DESC_ERR_UNSUPPORTED;
   }
   fclose(f);

@@ -847,14 +847,15 @@ hipError_t launch_bf16x3(const desc_gemm_problem* problems, int64_t G, const Bf1
 
 // FP32 tile choice: 128 x 128 tiles for problems with M, N >= 256 and 64 x 64
 // otherwise, or 64 x 64 tiles throughout, in the first tile form; or the mixed
-// tiles.  "tile64_rm_d2" is the name that older tables hold; the row-major 64 x 64
-// tiles it stood for are gone, and it selects the mixed ones too.
-constexpr const char* kNames[] = {"tile128_or_64", "tile64", "tile64_rm_d2", "mixed128_64"};
-constexpr int kMixed = 2;                       // this one and the next
+// tiles, which earlier tables know by the name of the row-major 64 x 64 tiles
+// that they replaced.
+constexpr const char* kNames[] = {"tile128_or_64", "tile64", "mixed128_64"};
+constexpr int kMixed = 2;
 constexpr int kDefaults[tune::kClasses] = {1, 1, 1, 1};
 constexpr int64_t kBigMin[] = {256, INT64_MAX};
 const bool kRegistered =
-    (tune::register_op(tune::kGemmGrouped, "gemm_grouped", 4, kNames, kDefaults), true);
+    (tune::register_op(tune::kGemmGrouped, "gemm_grouped", 3, kNames, kDefaults),
+     tune::register_earlier_name(tune::kGemmGrouped, "tile64_rm_d2", kMixed), true);
 
 constexpr const char* kNamesBf16[] = {"tile64", "tile128", "fused64", "fused128"};
 constexpr int kDefaultsBf16[tune::kClasses] = {3, 3, 3, 3};
@@ -919,7 +920,7 @@ hipError_t gemm_grouped_f32(const desc_gemm_problem* problems, int64_t G, void* 
   const GroupedWs w = carve(ws, G);
   // the size class is taken from the problem count
   const int cfg = tune::get(tune::kGemmGrouped, tune::size_class(tune::kGemmGrouped, G));
-  if (cfg >= kMixed) {
+  if (cfg == kMixed) {
     static int mixed_grid[64] = {0};
     const MixWs m{w.total, w.tile_start, w.big, w.order};
     const int grid = launch::resident_grid(grouped_mixed_kernel, mixed_grid, 1, kBlock);

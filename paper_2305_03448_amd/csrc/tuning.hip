@@ -1,6 +1,8 @@
 // tuning.hip -- storage of the configuration table (host code only).
 #include "tuning.hpp"
 
+#include <string.h>
+
 #include <atomic>
 
 namespace desc {
@@ -12,6 +14,8 @@ struct Entry {
   int count = 0;
   const char* const* names = nullptr;
   int defaults[kClasses] = {0, 0, 0, 0};
+  const char* earlier = nullptr;
+  int earlier_cfg = -1;
   std::atomic<int> chosen[kClasses];
   Entry() {
     for (auto& c : chosen) c.store(-1);
@@ -32,6 +36,19 @@ void register_op(int op, const char* name, int count, const char* const* names,
   e.count = count;
   e.names = names;
   for (int c = 0; c < kClasses; ++c) e.defaults[c] = defaults[c];
+}
+
+void register_earlier_name(int op, const char* name, int cfg) {
+  entry(op).earlier = name;
+  entry(op).earlier_cfg = cfg;
+}
+
+int config_by_name(int op, const char* name) {
+  if (op < 0 || op >= kNumOps) return -1;
+  const Entry& e = entry(op);
+  for (int c = 0; c < e.count; ++c)
+    if (strcmp(e.names[c], name) == 0) return c;
+  return e.earlier && strcmp(e.earlier, name) == 0 ? e.earlier_cfg : -1;
 }
 
 int size_class(int op, int64_t size) {

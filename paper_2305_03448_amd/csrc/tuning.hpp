@@ -38,6 +38,10 @@ const char* op_name(int op);
 bool set(int op, int cls, int cfg);     // cfg < 0 restores the default
 void register_op(int op, const char* name, int count, const char* const* names,
                  const int* defaults);
+// A name that tables written earlier hold for configuration cfg (one per op).
+void register_earlier_name(int op, const char* name, int cfg);
+// The configuration of that name, earlier ones included; -1 if there is none.
+int config_by_name(int op, const char* name);
 
 }  // namespace tune
 }  // namespace desc
