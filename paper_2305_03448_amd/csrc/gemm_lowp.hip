@@ -1043,7 +1043,6 @@ constexpr const char* kNamesFp8[] = {"m128n128k128", "m128n128k64", "m256n128k12
                                      "m256n256k128_dma"};
 constexpr int kFp8ByShape = 9, kCountFp8 = (int)(sizeof(kNamesFp8) / sizeof(kNamesFp8[0]));
 constexpr int kDefaultsFp8[tune::kClasses] = {kFp8ByShape, kFp8ByShape, kFp8ByShape, kFp8ByShape};
-constexpr int kDefaults[tune::kClasses] = {0, 0, 0, 0};
 constexpr int kFp8Fused = 10, kFp8D64 = 12, kFp8Dma = 13;
 using Fp8D32 = DirectNtCfg<1, 1, 16, 2>;
 using Fp8D64 = DirectNtCfg<2, 2, 8, 1>;

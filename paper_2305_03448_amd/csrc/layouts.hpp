@@ -149,6 +149,19 @@ DESC_HD idx_t seg_of_unit(const V& unit_start, int64_t S, int64_t u) {
   }
   return lo;
 }
+// The same search by a whole wave, 64 entries a round: of the candidates
+// [lo, hi) lane l reads entry lo + l step, where it is one, and the entries
+// <= u are a prefix of the lanes, `le` of them.
+struct Search64 {
+  idx_t lo, hi;
+  DESC_HD bool done() const { return hi - lo <= 1; }
+  DESC_HD idx_t step() const { return (hi - lo + 63) >> 6; }
+  DESC_HD idx_t entry(idx_t lane) const { return lo + lane * step(); }
+  DESC_HD Search64 next(int le) const {
+    const idx_t s = step(), from = lo + (le - 1) * s;
+    return Search64{from, from + s < hi ? from + s : hi};
+  }
+};
 struct SegUnit {
   idx_t seg, j, begin, len;   // segment, unit index inside it, first position, length
   bool single;                // the segment has one unit only

@@ -2,6 +2,7 @@
 // problem (grouped.hip) or segment (segmented.hip) a global index belongs to.
 #pragma once
 #include "common.hpp"
+#include "layouts.hpp"
 #include "view.hpp"
 
 namespace desc {
@@ -15,15 +16,12 @@ template <class T>
 __device__ __forceinline__ idx_t wave_owner(const T* start, int64_t G, int64_t t) {
   auto st = array(start, G);
   const idx_t lane = lane_of_wave().index();
-  idx_t lo = 0, hi = G;
-  while (hi - lo > 1) {
-    const idx_t step = (hi - lo + kWave - 1) / kWave;
-    const idx_t i = lo + lane * step;
-    const bool le = i < hi && st[i] <= t;
-    lo += ((idx_t)__popcll(__ballot(le)) - 1) * step;
-    hi = lo + step < hi ? lo + step : hi;
+  layout::Search64 s{0, G};
+  while (!s.done()) {
+    const idx_t i = s.entry(lane);
+    s = s.next(__popcll(__ballot(i < s.hi && st[i] <= t)));
   }
-  return lo;
+  return s.lo;
 }
 
 }  // namespace desc
