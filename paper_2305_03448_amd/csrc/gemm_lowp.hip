@@ -1105,8 +1105,14 @@ hipError_t split_bf16_cols(const float* B, int64_t K, int64_t N, int64_t ldb, ui
 
 hipError_t quant_e4m3_rows(const float* A, int64_t M, int64_t K, int64_t lda, uint8_t* q,
                            int64_t ldq, float* scale, hipStream_t s) {
-  hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)M), dim3(kBlock), 0, s, A, M, K, lda, q, K,
-                     ldq, scale, f4_ok(A, lda), w_ok(q, ldq, 1));
+  // a block a row, at most as many rows a launch as one grid counts
+  constexpr int64_t kRows = int64_t(1) << 23;
+  const bool vec_in = f4_ok(A, lda), vec_out = w_ok(q, ldq, 1);
+  for (int64_t r = 0; r < M; r += kRows) {
+    const int64_t rows = M - r < kRows ? M - r : kRows;
+    hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)rows), dim3(kBlock), 0, s, A + r * lda,
+                       rows, K, lda, q + r * ldq, K, ldq, scale + r, vec_in, vec_out);
+  }
   return hipGetLastError();
 }
 

@@ -105,3 +105,20 @@ def test_fp8_column_codes_of_many_columns(K):
     for at in range(0, N, 1023):
         n = min(1023, N - at)
         assert torch.equal(q[at:at + n], want_q[:n]) and torch.equal(s[at:at + n], want_s[:n]), at
+
+
+def test_row_codes_of_many_rows():
+    M, K = (1 << 24) + 5, 4
+    case(f"quant e4m3 rows {M}x{K}")
+    g = torch.Generator(device=dev()).manual_seed(85)
+    part = torch.randn(4099, K, device=dev(), generator=g)
+    A = part.repeat(-(-M // 4099), 1)[:M].contiguous()
+    q = torch.full((M + 1, K), 0x55, dtype=torch.uint8, device=dev())
+    s = torch.full((M + 1,), -7.0, device=dev())
+    desc.desc_quant_e4m3_rows(A, q[:M], s[:M])
+    want_q = torch.empty(4099, K, dtype=torch.uint8, device=dev())
+    want_s = torch.empty(4099, device=dev())
+    desc.desc_quant_e4m3_rows(part, want_q, want_s)
+    assert torch.equal(q[:M], want_q.repeat(-(-M // 4099), 1)[:M])
+    assert torch.equal(s[:M], want_s.repeat(-(-M // 4099))[:M])
+    assert bool((q[M] == 0x55).all()) and float(s[M]) == -7.0
