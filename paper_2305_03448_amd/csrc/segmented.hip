@@ -163,10 +163,10 @@ struct UnitInfo {
 constexpr int64_t kScalarSearch = 64;
 template <class C>
 __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t* unit_start,
-                                          int64_t n, int64_t S, int64_t total, UnitInfo* out) {
+                                          int64_t n, int64_t S, int64_t total, idx_t u,
+                                          UnitInfo* out) {
   __shared__ int64_t s_info[5];
   auto thread = thread_x<C::block>();
-  const idx_t u = block_x().index();
   if (u >= total) return false;
   if (thread.index() < kWave) {
     const auto us = array(unit_start, S + 1);
@@ -343,10 +343,11 @@ __global__ __launch_bounds__(C::block) void seg_reduce_kernel(const int32_t* __r
                                                             int64_t S,
                                                             const int64_t* __restrict__ total,
                                                             const int64_t* __restrict__ unit_start,
-                                                            int64_t* __restrict__ out) {
+                                                            int64_t* __restrict__ out,
+                                                            int64_t block0) {
   __shared__ int64_t s_w[C::waves];
   UnitInfo ui;
-  if (!unit_info<C>(offsets, unit_start, n, S, total[0], &ui)) return;
+  if (!unit_info<C>(offsets, unit_start, n, S, total[0], block0 + block_x().index(), &ui)) return;
   const int64_t t = reduce_unit<C>(in, ui, s_w);
   if (thread_x<C::block>().index() == 0) {
     auto o = array(out, S);
@@ -622,11 +623,12 @@ __global__ __launch_bounds__(C::block) __attribute__((amdgpu_waves_per_eu(C::rou
 void seg_scan_kernel(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
                      const int64_t* __restrict__ offsets, int64_t S,
                      const int64_t* __restrict__ total, const int64_t* __restrict__ unit_start,
-                     uint64_t* __restrict__ status, WsHeader* __restrict__ hdr) {
+                     uint64_t* __restrict__ status, WsHeader* __restrict__ hdr, int64_t block0) {
   __shared__ ScanShared sh;
   UnitInfo ui;
-  if (!unit_info<C>(offsets, unit_start, n, S, total[0], &ui)) return;
-  scan_unit<C>(in, out, ui, block_x().index(), status,
+  const idx_t u = block0 + block_x().index();
+  if (!unit_info<C>(offsets, unit_start, n, S, total[0], u, &ui)) return;
+  scan_unit<C>(in, out, ui, u, status,
                max_polls(__hip_atomic_load(&hdr->wait_limit, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT)),
                hdr, sh);
@@ -781,10 +783,10 @@ template <class C>
 __global__ __launch_bounds__(C::block) void seg_reduce_short_kernel(
     const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ offsets, int64_t S,
     const int64_t* __restrict__ total, int64_t max_units, const int64_t* __restrict__ unit_start,
-    int64_t* __restrict__ out) {
+    int64_t* __restrict__ out, int64_t block0) {
   __shared__ BlockUnits<C> bu;
   __shared__ int64_t s_w[C::waves];
-  const auto mine = layout::block_units<C::waves>(block_x().index(), total[0], max_units);
+  const auto mine = layout::block_units<C::waves>(block0 + block_x().index(), total[0], max_units);
   if (mine.count <= 0) return;
   find_units<C>(offsets, unit_start, n, S, mine, bu);
   auto thread = thread_x<C::block>();
@@ -819,13 +821,13 @@ __global__ __launch_bounds__(C::block) void seg_scan_short_kernel(
     const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
     const int64_t* __restrict__ offsets, int64_t S, const int64_t* __restrict__ total,
     int64_t max_units, const int64_t* __restrict__ unit_start, uint64_t* __restrict__ status,
-    WsHeader* __restrict__ hdr) {
+    WsHeader* __restrict__ hdr, int64_t block0) {
   __shared__ BlockUnits<C> bu;
   __shared__ union {
     ScanShared one;
     RunShared<C> run;
   } sh;
-  const auto mine = layout::block_units<C::waves>(block_x().index(), total[0], max_units);
+  const auto mine = layout::block_units<C::waves>(block0 + block_x().index(), total[0], max_units);
   if (mine.count <= 0) return;
   find_units<C>(offsets, unit_start, n, S, mine, bu);
   auto thread = thread_x<C::block>();
@@ -952,6 +954,17 @@ int scan_by_mean(int64_t n, int64_t S) {
   return n <= kUnit16Scan * S ? 1 : 2;
 }
 
+// `blocks` blocks in as many launches as one grid's count of threads asks for
+// (one below 2^22 blocks); a unit waits only for units of earlier blocks, so of
+// this launch or one before it.
+template <class C, class F>
+hipError_t in_grids(int64_t blocks, F&& launch) {
+  constexpr int64_t kBlocks = int64_t(0xFFFFFFFF) / C::block;
+  for (int64_t b = 0; b < blocks; b += kBlocks)
+    launch(dim3((unsigned)(blocks - b < kBlocks ? blocks - b : kBlocks)), b);
+  return hipGetLastError();
+}
+
 template <class C>
 hipError_t launch_reduce(const int32_t* in, int64_t n, const int64_t* offsets, int64_t S,
                          int64_t* out, void* ws, hipStream_t s, bool persistent) {
@@ -969,14 +982,15 @@ hipError_t launch_reduce(const int32_t* in, int64_t n, const int64_t* offsets, i
   }
   hipLaunchKernelGGL((plan_kernel<C, false>), dim3(1), dim3(kPlanBlock), 0, s, offsets, n, S,
                      w.total, w.unit_start, out, (uint64_t*)nullptr, (int64_t)0);
-  if (units > 0 && many_short)
-    hipLaunchKernelGGL(seg_reduce_short_kernel<C>,
-                       dim3((unsigned)((units + C::waves - 1) / C::waves)), dim3(C::block), 0, s,
-                       in, n, offsets, S, w.total, units, w.unit_start, out);
-  else if (units > 0)
-    hipLaunchKernelGGL(seg_reduce_kernel<C>, dim3((unsigned)units), dim3(C::block), 0, s, in, n,
-                       offsets, S, w.total, w.unit_start, out);
-  return hipGetLastError();
+  if (many_short)
+    return in_grids<C>((units + C::waves - 1) / C::waves, [&](dim3 grid, int64_t block0) {
+      hipLaunchKernelGGL(seg_reduce_short_kernel<C>, grid, dim3(C::block), 0, s, in, n, offsets, S,
+                         w.total, units, w.unit_start, out, block0);
+    });
+  return in_grids<C>(units, [&](dim3 grid, int64_t block0) {
+    hipLaunchKernelGGL(seg_reduce_kernel<C>, grid, dim3(C::block), 0, s, in, n, offsets, S, w.total,
+                       w.unit_start, out, block0);
+  });
 }
 
 // The scan stays in the two-launch form: in a persistent grid the units of
@@ -990,14 +1004,15 @@ hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, const int64_t
   const int64_t mu = S + (n + C::unit - 1) / C::unit;
   hipLaunchKernelGGL((plan_kernel<C, true>), dim3(1), dim3(kPlanBlock), 0, s, offsets, n, S,
                      w.total, w.unit_start, (int64_t*)nullptr, w.status, mu);
-  if (mu > 0 && short_scan(n, S))
-    hipLaunchKernelGGL(seg_scan_short_kernel<C>,
-                       dim3((unsigned)((mu + C::waves - 1) / C::waves)), dim3(C::block), 0, s, in,
-                       out, n, offsets, S, w.total, mu, w.unit_start, w.status, (WsHeader*)ws);
-  else if (mu > 0)
-    hipLaunchKernelGGL(seg_scan_kernel<C>, dim3((unsigned)mu), dim3(C::block), 0, s, in, out, n,
-                       offsets, S, w.total, w.unit_start, w.status, (WsHeader*)ws);
-  return hipGetLastError();
+  if (short_scan(n, S))
+    return in_grids<C>((mu + C::waves - 1) / C::waves, [&](dim3 grid, int64_t block0) {
+      hipLaunchKernelGGL(seg_scan_short_kernel<C>, grid, dim3(C::block), 0, s, in, out, n, offsets,
+                         S, w.total, mu, w.unit_start, w.status, (WsHeader*)ws, block0);
+    });
+  return in_grids<C>(mu, [&](dim3 grid, int64_t block0) {
+    hipLaunchKernelGGL(seg_scan_kernel<C>, grid, dim3(C::block), 0, s, in, out, n, offsets, S,
+                       w.total, w.unit_start, w.status, (WsHeader*)ws, block0);
+  });
 }
 
 // The reduce has no 64K unit: holding 16 rounds in 1024 threads spills.

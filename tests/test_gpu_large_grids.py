@@ -122,3 +122,20 @@ def test_row_codes_of_many_rows():
     assert torch.equal(q[:M], want_q.repeat(-(-M // 4099), 1)[:M])
     assert torch.equal(s[:M], want_s.repeat(-(-M // 4099))[:M])
     assert bool((q[M] == 0x55).all()) and float(s[M]) == -7.0
+
+
+@pytest.mark.parametrize("B", [(1 << 24) + 3, (1 << 26) + 3])
+def test_many_rows_reduced_and_scanned(B):
+    """More segments than one grid counts, a block each or four to a block."""
+    L = 2
+    case(f"batched {B}x{L}")
+    x = (torch.arange(B * L, dtype=torch.int32, device=dev()) % 1021).view(B, L)
+    r = torch.full((B + 1,), 5, dtype=torch.int64, device=dev())
+    desc.desc_reduce_batched_i32(x, r[:B])
+    both = x[:, 0] + x[:, 1]
+    assert torch.equal(r[:B], both.long()) and int(r[B]) == 5
+    del r
+    y = torch.full((B + 1, L), -5, dtype=torch.int32, device=dev())
+    desc.desc_scan_batched_i32(x, y[:B])
+    assert torch.equal(y[:B, 0], x[:, 0]) and torch.equal(y[:B, 1], both)
+    assert bool((y[B] == -5).all())
