@@ -156,11 +156,17 @@ struct UnitInfo {
 
 // Unit u of this block, found by wave 0 and shared.  The 64-way search takes
 // two or three rounds of parallel loads where a binary search takes a dependent
-// load per step, 14 of them (8 us a block) at 16384 segments.  Up to 64 segments
-// the binary search is the faster one: its position is uniform, so its loads
-// are scalar ones that hit the scalar cache (reduce of 64 rows of 4 M 181
-// against 184 us, scan 416 / 422; 1000 rows of 60000 60 against 56).
-constexpr int64_t kScalarSearch = 64;
+// load per step, 14 of them (8 us a block) at 16384 segments.  Of few segments
+// the binary search is the faster one, since its position is uniform and its
+// loads are scalar ones that hit the scalar cache: up to 16 segments, and up to
+// 64 where the blocks come in many rounds (reduce of 64 rows of 4 M 181 against
+// 184 us, scan 416 / 422; 1000 rows of 60000 60 against 56).  In a scan of
+// 64 segments with one round of blocks its steps lie in the serial chain of the
+// call (262144 elements 8.2 against 7.5 us, 4.2 M 12.9 / 12.2).
+__device__ __forceinline__ bool scalar_search(int64_t S, int64_t units) {
+  constexpr int64_t kFewSegments = 16, kSomeSegments = 64, kManyUnits = 4096;
+  return S <= kFewSegments || (S <= kSomeSegments && units > kManyUnits);
+}
 template <class C>
 __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t* unit_start,
                                           int64_t n, int64_t S, int64_t total, idx_t u,
@@ -170,7 +176,7 @@ __device__ __forceinline__ bool unit_info(const int64_t* offsets, const int64_t*
   if (u >= total) return false;
   if (thread.index() < kWave) {
     const auto us = array(unit_start, S + 1);
-    const idx_t seg = S <= kScalarSearch ? layout::seg_of_unit(us, S, u)
+    const idx_t seg = scalar_search(S, total) ? layout::seg_of_unit(us, S, u)
                                          : wave_owner(unit_start, S, u);
     const layout::SegUnit su =
         layout::seg_unit_of(array(offsets, S + 1), us, n, C::unit, u, seg);
