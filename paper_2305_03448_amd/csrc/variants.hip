@@ -205,13 +205,18 @@ namespace launch {
 hipError_t reduce_blocks_i32(const int32_t* in, int64_t n, int64_t E, int64_t* out,
                              hipStream_t s) {
   const int64_t blocks = (n + E - 1) / E;
-  if (blocks == 0) return hipSuccess;
-  if ((((uintptr_t)in) & 15) == 0)
-    hipLaunchKernelGGL(reduce_blocks_kernel<true>, dim3((unsigned)blocks), dim3(kRBlock), 0, s,
-                       in, n, E, out);
-  else
-    hipLaunchKernelGGL(reduce_blocks_kernel<false>, dim3((unsigned)blocks), dim3(kRBlock), 0, s,
-                       in, n, E, out);
+  const bool vec = (((uintptr_t)in) & 15) == 0;
+  // at most as many chunks a launch as one grid counts
+  constexpr int64_t kMaxBlocks = int64_t(1) << 23;
+  for (int64_t b = 0; b < blocks; b += kMaxBlocks) {
+    const dim3 grid((unsigned)(blocks - b < kMaxBlocks ? blocks - b : kMaxBlocks));
+    if (vec)
+      hipLaunchKernelGGL(reduce_blocks_kernel<true>, grid, dim3(kRBlock), 0, s, in + b * E,
+                         n - b * E, E, out + b);
+    else
+      hipLaunchKernelGGL(reduce_blocks_kernel<false>, grid, dim3(kRBlock), 0, s, in + b * E,
+                         n - b * E, E, out + b);
+  }
   return hipGetLastError();
 }
 

@@ -139,3 +139,16 @@ def test_many_rows_reduced_and_scanned(B):
     desc.desc_scan_batched_i32(x, y[:B])
     assert torch.equal(y[:B, 0], x[:, 0]) and torch.equal(y[:B, 1], both)
     assert bool((y[B] == -5).all())
+
+
+def test_chunk_sums_of_many_chunks():
+    chunks, E = (1 << 24) + 3, 1024
+    case(f"chunk sums {chunks}x{E}")
+    x = torch.empty(chunks, E, dtype=torch.int32, device=dev())
+    ids = torch.arange(chunks, dtype=torch.int32, device=dev()) % 1021
+    x[:] = ids.view(-1, 1)
+    out = torch.full((chunks + 1,), -5, dtype=torch.int64, device=dev())
+    desc.desc_reduce_blocks_i32(x.view(-1)[:-1], E, out[:chunks])
+    want = ids.long() * E
+    want[-1] -= ids[-1]
+    assert torch.equal(out[:chunks], want) and int(out[chunks]) == -5
