@@ -50,9 +50,9 @@ STEP_BYTES = SCAN_BYTES + TRANSPOSE_BYTES
 # (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0), taken for ScanCfg<1024, 16, true>
 # built from the sources whose hash is SCAN_TRAFFIC_SRC_HASH; reported as
 # None once the kernel's sources (or its configuration) have changed.
-SCAN_TRAFFIC_BYTES = 2151956796
+SCAN_TRAFFIC_BYTES = 2151857979
 SCAN_TRAFFIC_CONFIG = "b1024_r16_nt"
-SCAN_TRAFFIC_SRC_HASH = "2cb6e096ec786a71"
+SCAN_TRAFFIC_SRC_HASH = "2b9a2b9906b9b967"
 SCAN_SOURCES = ("scan.hip", "lookback.hpp", "common.hpp", "layouts.hpp", "view.hpp", "wave.hpp")
 
 

@@ -15,10 +15,10 @@
 // kWK waves share one tile and take its stages in turn (wave w the stages w,
 // w + kWK, ...); their partial sums meet in LDS and are added in wave order,
 // so the result depends on the shape only.  Without a staging buffer a tile
-// can be as small as the shape asks for: 1000 x 1500 x 777 takes 29 us as 256
-// tiles of 64 x 96 against 94 us as 96 LDS-staged tiles of 128 x 128 (whose
-// rows, 777 words, it loads one by one), 32 x 4096 x 4096 23 us against 158,
-// 64 x 64 x 4096 12 against 123, 512^3 6.8 against 19.5.
+// can be as small as the shape asks for: 1000 x 1500 x 777 takes 25 us as 256
+// tiles of 64 x 96 against 92 us as 96 LDS-staged tiles of 128 x 128 (whose
+// rows, 777 words, it loads one by one), 32 x 4096 x 4096 18.7 us against 154,
+// 64 x 64 x 4096 11.9 against 123, 512^3 6.4 against 19.5.
 //
 // Edges without branches: a row past M reads row M - 1 (its results are not
 // stored); a column group that would cross N starts at N - FN instead, for
@@ -50,7 +50,7 @@ struct DirectCfg {
 };
 
 // Strides the direct form accepts: its 32-bit byte offsets span at most 64
-// rows of A, or 16 rows of B and one row's columns.
+// rows of A, or 32 rows of B (16 in FP32 products) and one row's columns.
 constexpr int64_t kDirectMaxLd = int64_t(1) << 23;
 
 namespace gemm_direct {

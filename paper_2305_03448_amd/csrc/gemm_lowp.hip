@@ -1,7 +1,9 @@
 // gemm_lowp.hip -- the precision forms of C = A * B: three-product split
 // bfloat16 with FP32 accumulation, and e4m3 with per-row / per-column
-// absmax scaling.  Both prepare their operands in the workspace and then run
-// the NT matrix-core tile of gemm_nt.hpp.
+// absmax scaling.  Large products prepare their operands in the workspace and
+// run direct-to-LDS tiles (gemm_dma.hpp) or the NT tile of gemm_nt.hpp over
+// them; small ones take the FP32 operands or, in FP8, direct tiles over the
+// codes (gemm_direct.hpp, gemm_fp8_fused.hpp, gemm_direct_nt.hpp).
 //
 // BF16x3.  a = hi + lo with hi = bf16(a), lo = bf16(a - hi) (a - hi is exact
 // in FP32), likewise for b; C ~ Ah*Bh + Ah*Bl + Al*Bh (the Al*Bl term is
@@ -18,7 +20,8 @@
 // Pre-pass, two launches: one block per row of A (absmax, then encode)
 // beside the column absmax of B as partial maxima over K slices; then a pass
 // over B that encodes with the column scales and writes q^T as [Np][Kp].  Up
-// to K = 2048 one launch does both (fp8_once_kernel).
+// to K = 2048 one launch does both (fp8_once_kernel), but for a wide B of
+// short K (wide_b).
 //
 // Padding: Mp, Np are multiples of 256 and Kp a multiple of 128 elements;
 // the pre-pass writes zeros there, so the GEMM main loop has no guards.

@@ -5,16 +5,18 @@
 // Problem g is C_g = A_g * B_g with its own M, N, K, leading dimensions and
 // pointers, described in a device array.
 //
-//   plan kernel (one block): gives each problem a tile shape (128 x 128 when
-//     both M and N are at least 256, else 64 x 64; or 64 x 64 throughout, by
-//     the tuning table), orders the problems longest tiles first -- the
-//     large tiles, then by K in buckets of 64 -- so that the long tiles start
-//     early and the short ones fill in at the end, and writes the exclusive
-//     prefix of tile counts in that order with the total to the workspace.
+//   plan kernel (one block): gives each problem its tiles (by default whole
+//     128 x 128 tiles with 64 x 64 ones on the strips they leave, where the
+//     call has enough large ones, else 64 x 64 throughout; a configuration of
+//     one shape a problem and one of 64 x 64 throughout are left), orders the
+//     problems longest tiles first -- the large tiles, then by K in buckets of
+//     64 -- so that the long tiles start early and the short ones fill in at
+//     the end, and writes the exclusive prefix of tile counts in that order
+//     with the total to the workspace.
 //   main kernel: a grid of as many blocks as fit on the device at once walks
-//     the global tile sequence, runs of 64 consecutive tiles per XCD so that
-//     a problem's tiles share one L2; a binary search over the prefix finds
-//     the problem, and the FP32 matrix-core tile routine of the plain GEMM
+//     the global tile sequence, runs of 64 consecutive tiles per XCD (16 of
+//     the default's large ones) so that a problem's tiles share one L2; a
+//     search over the prefix, 64 entries a step, finds the problem, and the FP32 matrix-core tile routine of the plain GEMM
 //     computes the tile.  Tiles are independent, so the loop needs no
 //     inter-block communication.
 #include "common.hpp"

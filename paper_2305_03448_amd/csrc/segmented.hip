@@ -6,8 +6,8 @@
 // units of at most UNIT consecutive elements (an empty segment gives none);
 // UNIT is 8K to 64K elements, picked per size class by the tuning table or from
 // the mean segment length (below).
-// A unit finds its segment by binary search over the exclusive prefix of the
-// unit counts, loads its elements with dword-aligned 16-byte loads (segments
+// A unit finds its segment by a search over the exclusive prefix of the unit
+// counts (64 entries a step, or two where the segments are few), loads its elements with dword-aligned 16-byte loads (segments
 // start anywhere), and
 //   reduce: sums them in int64; a segment of one unit stores its sum, the
 //           units of a longer one combine theirs (below);
